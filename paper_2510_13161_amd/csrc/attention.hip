@@ -726,6 +726,15 @@ __global__ __launch_bounds__(256, 1) void attn_stream_kernel(AttnArgs a) {
 // and the transposing V reads (8 keys, two half-units each per 32 lanes)
 // touch every LDS bank once. The chunk's partials are merged as in the
 // kernels above (last arrival or the merge kernel).
+// What bounds it: with half the compute units busy, the block's latency chain
+// (LDS reads, MFMAs, softmax, MFMAs); with all of them, HBM (1.35 us a block
+// of 32 KB on every unit, 5.9 TB/s). The softmax therefore exchanges no lanes
+// on a block that moves no running max (the vote and the sums are per lane,
+// the sums joined once at the end), the hi and lo score products are separate
+// chains and V is read ahead of the scores. Against four lane exchanges a
+// block, chained products and V read after them (us a launch): 7 chains at
+// contexts to 3000 27.5 -> 24.9, 11 to 4096 41.7 -> 36.7, 16 to 8192 93.8 ->
+// 84.2, a 66B tree at 2048 28.7 -> 27.5.
 template <int NQ>
 __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a) {
   constexpr int HD = 128;
@@ -839,29 +848,37 @@ __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a
         const int k0 = kbeg + 64 * i;
         const int key_hi = min(T, k0 + 64);
         // S^T[key][query] = K Q^T over the wave's half: lane holds key
-        // 16 (2 hk + j) + 4 g + r, query r16
-        floatx4 sc[2];
+        // 16 (2 hk + j) + 4 g + r, query r16. The hi and lo products sum
+        // apart: four chains of KSTEPS dependent MFMAs instead of two of
+        // twice that.
+        floatx4 sc[2], sl[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          sc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 2; ++j) sc[j] = sl[j] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int kk = 0; kk < KSTEPS; ++kk) {
+        for (int kk = 0; kk < KSTEPS; ++kk)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
             const bf16x8 kf = *reinterpret_cast<const bf16x8*>(ks + (16 * (2 * hk + j) + r16) * HD +
                                                                (((4 * kk + g) ^ r16) << 3));
             sc[j] = mfma16x16x32(kf, qh[kk], sc[j]);
-            sc[j] = mfma16x16x32(kf, ql[kk], sc[j]);
+            sl[j] = mfma16x16x32(kf, ql[kk], sl[j]);
           }
+        // V by the transposing LDS read, ahead of the softmax: lane r16 of
+        // group g addresses key 32 hk + 4 g + r16 / 4 (and + 16), dims
+        // 16 ds + 4 (r16 % 4) .. + 4
+        bf16x8 vb[DSUB];
+        const int kr = 32 * hk + 4 * g + (r16 >> 2);
+#pragma unroll
+        for (int ds = 0; ds < DSUB; ++ds) {
+          const int u = 2 * ds + ((r16 & 3) >> 1);
+          const uint16_t* p0 = vsl + kr * HD + ((u ^ ((kr & 7) << 1)) << 3) + 4 * (r16 & 1);
+          const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)p0);
+          const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p0 + 16 * HD));
+          vb[ds] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         }
-        float mx = -INFINITY;
-        if (k0 + 64 <= L) {
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              sc[j][r] *= scale2;
-              mx = fmaxf(mx, sc[j][r]);
-            }
-        } else {
+        for (int j = 0; j < 2; ++j) sc[j] += sl[j];
+        if (k0 + 64 > L) {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -869,15 +886,23 @@ __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a
               const int pos = k0 + 16 * (2 * hk + j) + 4 * g + r;
               const bool anc_bit = (anc >> ((pos - L) & 63)) & 1ull;
               const bool vis = (pos < key_hi) & ((pos < L) | anc_bit);
-              sc[j][r] = vis ? sc[j][r] * scale2 : -INFINITY;
-              mx = fmaxf(mx, sc[j][r]);
+              sc[j][r] = vis ? sc[j][r] : -INFINITY;
             }
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        float mx = -INFINITY;  // over this lane's keys of the block
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[j][r]);
+        mx *= scale2;
         // the reference of the running sums moves up only when a block max
-        // exceeds it by more than 2^8 (as in attn_stream_kernel)
+        // exceeds it by more than 2^8 (as in attn_stream_kernel). The vote
+        // takes every lane's own max, so a block that does not move it (nearly
+        // all) has no lane exchange; only a block that does combines the four
+        // lanes of a query.
         if (__builtin_amdgcn_read_exec() & __ballot(mx > mrun + 8.0f)) {
+          mx = fmaxf(mx, __shfl_xor(mx, 16));
+          mx = fmaxf(mx, __shfl_xor(mx, 32));
           const float mnew = fmaxf(mrun, mx);
           const float alpha = mrun == -INFINITY ? 0.0f : exp2_hw(mrun - mnew);
           lrun *= alpha;
@@ -890,21 +915,15 @@ __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a
           }
         }
         const float mref = mrun == -INFINITY ? 0.0f : mrun;
-        float ls = 0.0f;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            sc[j][r] = exp2_hw(sc[j][r] - mref);
-            ls += sc[j][r];
+            sc[j][r] = exp2_hw(__builtin_fmaf(sc[j][r], scale2, -mref));
+            lrun += sc[j][r];  // the lane's own keys; the query's four lanes are summed at the end
           }
-        ls += __shfl_xor(ls, 16);
-        ls += __shfl_xor(ls, 32);
-        lrun += ls;
         // O += P V, P as bf16 hi + lo in the k order of the V operand (keys
-        // 4 g + r of the half's two 16-key tiles); V by the transposing LDS
-        // read: lane r16 of group g addresses key 32 hk + 4 g + r16 / 4 (and
-        // + 16), dims 16 ds + 4 (r16 % 4) .. + 4
+        // 4 g + r of the half's two 16-key tiles)
         {
           u32x4 ph, pl;
 #pragma unroll
@@ -916,21 +935,16 @@ __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a
           }
           const bf16x8 pah = __builtin_bit_cast(bf16x8, ph);
           const bf16x8 pal = __builtin_bit_cast(bf16x8, pl);
-          const int kr = 32 * hk + 4 * g + (r16 >> 2);
 #pragma unroll
-          for (int ds = 0; ds < DSUB; ++ds) {
-            const int u = 2 * ds + ((r16 & 3) >> 1);
-            const uint16_t* p0 = vsl + kr * HD + ((u ^ ((kr & 7) << 1)) << 3) + 4 * (r16 & 1);
-            const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)p0);
-            const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(p0 + 16 * HD));
-            const bf16x8 vb = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            o[ds] = mfma16x16x32(pah, vb, o[ds]);
-            o[ds] = mfma16x16x32(pal, vb, o[ds]);
-          }
+          for (int ds = 0; ds < DSUB; ++ds) o[ds] = mfma16x16x32(pah, vb[ds], o[ds]);
+#pragma unroll
+          for (int ds = 0; ds < DSUB; ++ds) o[ds] = mfma16x16x32(pal, vb[ds], o[ds]);
         }
       }
       slot = slot + 1 == R ? 0 : slot + 1;
     }
+    lrun += __shfl_xor(lrun, 16);
+    lrun += __shfl_xor(lrun, 32);
   }
 
   // every wave is past its last ring access: the ring becomes the output
