@@ -155,13 +155,15 @@ typedef struct msd_model msd_model;
  * always, 0 never; unset, from 6 chunks on),
  * MSD_ROWS_MIN_MT (row tiles from which GEMMs with 256 or more 64-column
  * tiles may run the kernel that shares the activation through LDS: 3 unset;
- * it runs where its workgroups balance the compute units),
+ * at 3 it runs where its workgroups balance the compute units),
  * MSD_ROWS_MIN_TILES (forces that kernel on GEMMs with at least this many
  * tiles), MSD_ROWS_MAX_SPLITS (its splits of K at most, 4 unset) and
  * MSD_ROWS_NARROW (narrower GEMMs of 3 or more row tiles in that kernel
  * with many splits and their split sum and epilogue in a second kernel: 0
- * never, 2 at any size; unset, for matrices of 32M weights or more) and
- * MSD_ROWS_NARROW_MT (the row tiles from which that applies: 3 unset). */
+ * never, 2 at any size; unset, for matrices of 32M weights or more at 3 row
+ * tiles and of more than 24M from 4 on; smaller ones run whole K in groups of
+ * row tiles) and MSD_ROWS_NARROW_MT (the row tiles from which that applies:
+ * 3 unset). */
 msd_status msd_model_create(const msd_model_config* cfg, const void* const* tensors,
                             int32_t n_tensors, msd_model** out);
 void msd_model_destroy(msd_model* model);

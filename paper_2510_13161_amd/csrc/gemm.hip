@@ -153,15 +153,21 @@ __device__ __forceinline__ int row_len(const GemmArgs& a, int m) {
 }
 
 // the pre-norm summaries of the lane's row of row tile mt
-__device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, EpiIn& in) {
+// (PER of them a lane at most; groups of 4 past the last summary are skipped
+// by a branch the whole wave takes)
+template <int PER>
+__device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, float2 (&st)[PER]) {
   const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
   const int m = 16 * mt + r16;
   const int mm = m < a.M ? m : 0;
-  if (a.norm.kind != 0) {
+  if (a.norm.kind == 0) return;
 #pragma unroll
-    for (int i = 0; i < kMaxPer; ++i) {
+  for (int i0 = 0; i0 < PER; i0 += 4) {
+    if (4 * i0 >= a.norm.tiles) continue;
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i) {
       const int tt = q + 4 * i;
-      in.st[i] = a.norm.stats[(size_t)(tt < a.norm.tiles ? tt : 0) * a.M + mm];
+      st[i] = a.norm.stats[(uint32_t)(tt < a.norm.tiles ? tt : 0) * (uint32_t)a.M + mm];
     }
   }
 }
@@ -171,7 +177,7 @@ __device__ __forceinline__ void epi_load(const GemmArgs& a, int t, int mt, EpiIn
   const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
   const int m = 16 * mt + r16;
   const int mm = m < a.M ? m : 0;
-  if constexpr (has_norm<EPI>() && NORM) stats_load(a, mt, in);
+  if constexpr (has_norm<EPI>() && NORM) stats_load(a, mt, in.st);
   if constexpr (EPI == EPI_RESID) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -219,7 +225,8 @@ __device__ __forceinline__ void epi_load(const GemmArgs& a, int t, int mt, EpiIn
 // (the exact merge of equal-count groups). The four lanes of a row each hold
 // every fourth summary and their partial sums are combined by a butterfly,
 // which gives all four lanes identical bits.
-__device__ __forceinline__ void norm_finish(const GemmArgs& a, const EpiIn& in, float& mu,
+template <int PER>
+__device__ __forceinline__ void norm_finish(const GemmArgs& a, const float2 (&st)[PER], float& mu,
                                             float& rs) {
   const int q = (threadIdx.x & 63) >> 4;
   const RowNorm& nm = a.norm;
@@ -228,18 +235,26 @@ __device__ __forceinline__ void norm_finish(const GemmArgs& a, const EpiIn& in, 
   if (nm.kind == 0) return;
   float sm = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kMaxPer; ++i)
-    if (q + 4 * i < nm.tiles) sm += in.st[i].x;
+  for (int i0 = 0; i0 < PER; i0 += 4) {
+    if (4 * i0 >= nm.tiles) continue;
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i)
+      if (q + 4 * i < nm.tiles) sm += st[i].x;
+  }
   sm += __shfl_xor(sm, 16);
   sm += __shfl_xor(sm, 32);
   const float mean = sm / (float)nm.tiles;
   float m2 = 0.0f;
 #pragma unroll
-  for (int i = 0; i < kMaxPer; ++i)
-    if (q + 4 * i < nm.tiles) {
-      const float dv = in.st[i].x - mean;
-      m2 += in.st[i].y + (float)kTileN * dv * dv;
-    }
+  for (int i0 = 0; i0 < PER; i0 += 4) {
+    if (4 * i0 >= nm.tiles) continue;
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i)
+      if (q + 4 * i < nm.tiles) {
+        const float dv = st[i].x - mean;
+        m2 += st[i].y + (float)kTileN * dv * dv;
+      }
+  }
   m2 += __shfl_xor(m2, 16);
   m2 += __shfl_xor(m2, 32);
   const float var = m2 / (float)a.K;
@@ -248,6 +263,20 @@ __device__ __forceinline__ void norm_finish(const GemmArgs& a, const EpiIn& in, 
   } else {
     rs = 1.0f / sqrtf(var + nm.eps);
     mu = mean;
+  }
+}
+
+// (mu, r) of the lane's row of row tile mt, with registers for the summaries
+// of rows up to 5120 columns or up to 10240
+__device__ __forceinline__ void row_norm(const GemmArgs& a, int mt, float& mu, float& rs) {
+  if (a.norm.tiles <= 80) {
+    float2 st[20];
+    stats_load(a, mt, st);
+    norm_finish(a, st, mu, rs);
+  } else {
+    float2 st[kMaxPer];
+    stats_load(a, mt, st);
+    norm_finish(a, st, mu, rs);
   }
 }
 
@@ -518,6 +547,19 @@ __device__ void epi_head(const GemmArgs& a, int t, int mt, const floatx4 (&acc)[
   }
 }
 
+// the epilogue of a row tile, its inputs and the rows' norms at hand
+template <int EPI, int JT>
+__device__ __forceinline__ void epilogue_apply(const GemmArgs& a, int t, int mt, const floatx4 (&acc)[JT], float* scr,
+                                               const EpiIn& in, float mu, float rs) {
+  if constexpr (EPI == EPI_SWIGLU) epi_swiglu<JT>(a, t, mt, acc, scr, mu, rs);
+  else if constexpr (EPI == EPI_HEAD) epi_head<JT>(a, t, mt, acc, mu, rs);
+  else if constexpr (EPI == EPI_QKV) epi_qkv<JT>(a, t, mt, acc, mu, rs, in);  // 64- or 32-column tiles
+  else if constexpr (JT == 4) {  // the other epilogues run on 64-column tiles only
+    if constexpr (EPI == EPI_RESID) epi_resid(a, t, mt, acc, scr, in);
+    else epi_relu(a, t, mt, acc, scr, mu, rs);
+  }
+}
+
 // The epilogue of row tile mt of a finished tile; `in` holds its inputs
 // when they were loaded ahead (one row tile), otherwise they are loaded here.
 // norm_sh: (mu, r) of the tile's 16 rows, already merged (then NLDS: the
@@ -538,41 +580,32 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& a, int t, int mt, 
       mu = v.x;
       rs = v.y;
     } else {
-      norm_finish(a, in, mu, rs);
+      norm_finish(a, in.st, mu, rs);
     }
   }
-  if constexpr (EPI == EPI_SWIGLU) epi_swiglu<JT>(a, t, mt, acc, scr, mu, rs);
-  else if constexpr (EPI == EPI_HEAD) epi_head<JT>(a, t, mt, acc, mu, rs);
-  else if constexpr (EPI == EPI_QKV) epi_qkv<JT>(a, t, mt, acc, mu, rs, in);  // 64- or 32-column tiles
-  else if constexpr (JT == 4) {  // the other epilogues run on 64-column tiles only
-    if constexpr (EPI == EPI_RESID) epi_resid(a, t, mt, acc, scr, in);
-    else epi_relu(a, t, mt, acc, scr, mu, rs);
-  }
+  epilogue_apply<EPI, JT>(a, t, mt, acc, scr, in, mu, rs);
 }
 
-// The epilogues of the row tiles a wave owns (row tile mt belongs to wave
-// mt % owners). At 9 row tiles one copy of the per-tile code runs in a loop
-// (unrolled, the 9 copies made the kernel 3.8 times larger and slower by a
-// little); each pass picks its row tile's accumulators by compile-time
-// index, so acc is never indexed at run time (that would put it in scratch
-// memory).
-template <int MT, int EPI, int JT, bool NLDS = false>
+// The epilogues of all row tiles of a wave's tile, norm_sh holding their
+// rows' norms. From 6 row tiles on one copy of the per-tile code runs in a loop
+// (unrolled, 9 copies made the kernel 3.8 times larger and slower by a
+// little); each pass picks its row tile's accumulators by compile-time index,
+// so acc is never indexed at run time (that would put it in scratch memory).
+template <int MT, int EPI, int JT, bool NLDS>
 __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, int t, const floatx4 (&acc)[MT][JT],
-                                              float* scr, int owner, int owners,
-                                              const float2* norm_sh = nullptr) {
+                                              float* scr, const float2* norm_sh) {
   if constexpr (MT <= 5) {
     // up to 5 row tiles: unrolled (the compact loop below costs these
     // variants their second wave per SIMD)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      if (mt % owners != owner) continue;
       EpiIn none;
       epilogue_tile<EPI, JT, false, NLDS>(a, t, mt, acc[mt], scr, none, NLDS ? norm_sh + 16 * mt : nullptr);
     }
     return;
   }
 #pragma clang loop unroll(disable)
-  for (int mt = owner; mt < MT; mt += owners) {
+  for (int mt = 0; mt < MT; ++mt) {
     floatx4 cur[JT];
 #pragma unroll
     for (int mm = 0; mm < MT; ++mm)
@@ -590,11 +623,20 @@ struct KStep {
   bf16x8 ah[MT], al[MT];
 };
 
-template <int MT, int NW, int EPI, int JT>
+// GROUPS: the row tiles in a.row_groups groups of at most MT, a workgroup per
+// (column tile, group), whole K. For matrices too small to fill the chip
+// otherwise: no split partials, hand-off or second kernel, and a wave
+// finishes one row tile at most. The weights are read once per group, mostly
+// from L2. Measured at a 0.6B-shaped layer, 72 rows (us, against split-K):
+// QKV 17.7 -> 11.7 (3 groups), O 17.0 -> 11.3 (5), gate+up 15.7 -> 11.7 (2),
+// down 20.5 -> 14.7 (5); at 144 rows 26.7 -> 12.7, 24.7 -> 11.3, 23.6 ->
+// 21.7, 29.7 -> 14.5.
+template <int MT, int NW, int EPI, int JT, bool GROUPS = false>
 __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel(GemmArgs a) {
   // k-steps in flight per wave (measured per shape with the k-step-major
   // layout: the 2-wave 128-column FFN up tiles 5, 8-wave split-K tiles 6)
-  constexpr int D = MT == 1 ? (JT == 8 ? (NW == 2 ? 5 : 4) : (JT == 2 ? 6 : (NW == 8 ? 4 : 8))) : (MT <= 3 ? 4 : 2);
+  constexpr int D = MT == 1 ? (JT == 8 ? (NW == 2 ? 5 : 4) : (JT == 2 ? 6 : (NW == 8 ? 4 : 8)))
+                            : (NW == 8 && MT == 2 ? 5 : 4);
   constexpr int RCH = MT < 3 ? MT : 3;  // row tiles per LDS reduction round
   constexpr int TF = MT * JT * 256;     // floats of one tile's partial
   __shared__ floatx4 red[NW][RCH * JT][kWave];
@@ -607,15 +649,26 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
   const int lane = threadIdx.x & 63;
   // wave-uniform (scalar) so that the k-loop branches and waits are scalar
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = blockIdx.x / a.splits, s = blockIdx.x - t * a.splits;
+  int t = blockIdx.x / a.splits, s = blockIdx.x - t * a.splits;
+  int mt0 = 0, nmt = MT;  // the workgroup's row tiles
+  if constexpr (GROUPS) {
+    // the groups of a column tile 8 workgroups apart: on one XCD, at the same
+    // time, so that they share its reads of the weights
+    const int q = blockIdx.x / (8 * a.row_groups), r = blockIdx.x - q * 8 * a.row_groups, rg = r >> 3;
+    t = 8 * q + (r & 7);
+    s = 0;
+    if (t >= a.n_tiles) return;
+    mt0 = a.MT * rg / a.row_groups;
+    nmt = a.MT * (rg + 1) / a.row_groups - mt0;
+  }
   if constexpr (norm_helper<MT, NW, EPI>()) {
     if (wave == NW) {
       // the row norm, while the other waves stream; then the reduction's two
       // barriers, which order the LDS write before the epilogue reads it
       EpiIn hin;
-      epi_load<EPI, true, JT>(a, t, 0, hin);
+      epi_load<EPI, true, JT>(a, t, mt0, hin);
       float mu, rs;
-      norm_finish(a, hin, mu, rs);
+      norm_finish(a, hin.st, mu, rs);
       if (lane < 16) norm_sh[lane] = make_float2(mu, rs);
       __syncthreads();
       __syncthreads();
@@ -637,7 +690,7 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
   // one row tile: the epilogue's inputs are loaded ahead (the sequence
   // length that addresses the rotary table before the k-loop)
   EpiIn in1;
-  if constexpr (MT == 1 && EPI == EPI_QKV) in1.L = row_len(a, lane & 15);
+  if constexpr (MT == 1 && EPI == EPI_QKV) in1.L = row_len(a, 16 * mt0 + (lane & 15));
 
   floatx4 acc[MT][JT];
 #pragma unroll
@@ -662,7 +715,9 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
     for (int j = 0; j < JT; ++j) x.w[j] = load_nt(wp[j] + (size_t)k * kstr);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const uint16_t* p = ap + (size_t)(k * MT + mt) * 1024;
+      // (a tile past the group's last re-reads its first; its sums are unused)
+      const uint16_t* p = GROUPS ? ap + (size_t)(k * a.MT + mt0 + (mt < nmt ? mt : 0)) * 1024
+                                 : ap + (size_t)(k * MT + mt) * 1024;
       x.ah[mt] = load16(p);
       x.al[mt] = load16(p + 512);
     }
@@ -710,7 +765,7 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
   }
 
   if constexpr (MT == 1) {
-    if (wave == 0) epi_load<EPI, !norm_helper<MT, NW, EPI>(), JT>(a, t, 0, in1);
+    if (wave == 0) epi_load<EPI, !norm_helper<MT, NW, EPI>(), JT>(a, t, mt0, in1);
   }
 
   if constexpr (MT == 1) {
@@ -782,7 +837,7 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
       if (lane == 0) counter_reset(&a.counters[t]);
     }
 
-    epilogue_tile<EPI, JT, true>(a, t, 0, acc[0], scr_all, in1,
+    epilogue_tile<EPI, JT, true>(a, t, mt0, acc[0], scr_all, in1,
                                  norm_helper<MT, NW, EPI>() ? norm_sh : nullptr);
   } else {
     // Several row tiles: row tile mt belongs to wave mt % NW, which sums it
@@ -850,7 +905,12 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
       }
       if (threadIdx.x == 0) counter_reset(&a.counters[t]);
     }
-    epilogue_rows<MT, EPI, JT>(a, t, acc, scr_all + wave * 16 * kScr, wave, NW);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      if (!mine(mt) || mt >= nmt) continue;
+      EpiIn none;
+      epilogue_tile<EPI, JT, false>(a, t, mt0 + mt, acc[mt], scr_all + wave * 16 * kScr, none);
+    }
   }
 }
 
@@ -872,7 +932,7 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
 // gemm_epi_kernel sums them and runs the epilogues.
 template <int MT>
 __host__ __device__ constexpr int rows_depth() {  // weight k-steps in flight per compute wave
-  return MT >= 9 ? 3 : (MT >= 5 ? 6 : 4);
+  return MT >= 8 ? 3 : (MT == 7 ? 4 : (MT >= 4 ? 6 : 4));
 }
 // Up to 3 row tiles two workgroups share a compute unit (their LDS rings fit
 // together): 10 waves, so up to 3 on a SIMD, 168 VGPRs each at most.
@@ -950,10 +1010,8 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
   // barrier 0 below orders the writes before any read
   if constexpr (has_norm<EPI>()) {
     for (int mt = wave; mt < MT; mt += NW) {
-      EpiIn nin;
-      stats_load(a, mt, nin);
       float mu, rs;
-      norm_finish(a, nin, mu, rs);
+      row_norm(a, mt, mu, rs);
       if (lane < 16) norm_sh[16 * mt + lane] = make_float2(mu, rs);
     }
   }
@@ -1056,46 +1114,85 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
       for (int j = 0; j < JT; ++j) *reinterpret_cast<floatx4*>(part + (mt * JT + j) * 256) = acc[mt][j];
     return;
   }
-  epilogue_rows<MT, EPI, JT, has_norm<EPI>()>(a, t, acc, scr_all + wave * 16 * kScr, 0, 1, norm_sh);
+  epilogue_rows<MT, EPI, JT, has_norm<EPI>()>(a, t, acc, scr_all + wave * 16 * kScr, norm_sh);
 }
 
 // The split sum and epilogue of gemm_rows_kernel with splits > 1, a kernel
-// of their own: one wave per (64-column tile, row tile) sums that row
-// tile's partials in split order and runs its epilogue, so that no wave sums
-// and finishes all row tiles of its tile in series, and narrow GEMMs can
-// take many splits of K (enough waves for the MFMA work of 144 rows).
-template <int MT, int EPI>
+// of their own, so that no wave sums and finishes all row tiles of its tile in
+// series, and narrow GEMMs can take many splits of K (enough waves for the
+// MFMA work of 144 rows). A (64-column tile, row tile) belongs to SW waves:
+// wave w sums the partials of splits w, w + SW, .. (all its loads in flight at
+// once), wave 0 joins the waves' sums in wave order and runs the epilogue,
+// whose other inputs it loaded meanwhile, and with SW = 4 wave 1 merges the
+// row norms.
+template <int EPI, int SW>
 __global__ __launch_bounds__(256) void gemm_epi_kernel(GemmArgs a) {
   constexpr int JT = 4;
-  constexpr int TF = MT * JT * 256;
-  __shared__ __attribute__((aligned(16))) float scr_all[4 * 16 * kScr];
+  constexpr int SB = 4;  // partials in flight per wave
+  __shared__ __attribute__((aligned(16))) float scr_all[(4 / SW) * 16 * kScr];
+  __shared__ floatx4 red[SW > 1 ? SW - 1 : 1][JT][kWave];
+  __shared__ float2 norm_sh[16];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int u = blockIdx.x * 4 + wave;
-  const int t = u / MT, mt = u - t * MT;
+  const int u = SW == 1 ? blockIdx.x * 4 + wave : blockIdx.x, w = SW == 1 ? 0 : wave;
+  const int t = u / a.MT, mt = u - t * a.MT;
   if (t >= a.n_tiles) return;
-  const float* part = a.partial + (size_t)t * a.splits * TF + (mt * JT) * 256 + lane * 4;
+  const uint32_t TF = (uint32_t)a.MT * JT * 256;
+  const float* part = a.partial + (size_t)t * a.splits * TF + mt * JT * 256 + lane * 4;
+  EpiIn in;
+  if constexpr (EPI == EPI_QKV) in.L = row_len(a, 16 * mt + (lane & 15));
   floatx4 acc[JT];
 #pragma unroll
   for (int j = 0; j < JT; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  constexpr int SB = 4;  // splits' partials in flight
-  for (int sp0 = 0; sp0 < a.splits; sp0 += SB) {
+  for (int s0 = w; s0 < a.splits; s0 += SW * SB) {
     floatx4 pv[SB][JT];
 #pragma unroll
     for (int q = 0; q < SB; ++q) {
-      const int sp = sp0 + q < a.splits ? sp0 + q : sp0;
+      const int sp = s0 + q * SW < a.splits ? s0 + q * SW : s0;
 #pragma unroll
       for (int j = 0; j < JT; ++j)
-        pv[q][j] = *reinterpret_cast<const floatx4*>(part + (size_t)sp * TF + j * 256);
+        pv[q][j] = *reinterpret_cast<const floatx4*>(part + sp * TF + j * 256);
     }
+    if (s0 == 0) epi_load<EPI, false, JT>(a, t, mt, in);
 #pragma unroll
     for (int q = 0; q < SB; ++q)
-      if (sp0 + q < a.splits)
+      if (s0 + q * SW < a.splits)
 #pragma unroll
         for (int j = 0; j < JT; ++j) acc[j] += pv[q][j];
   }
-  EpiIn none;
-  epilogue_tile<EPI, JT, false>(a, t, mt, acc, scr_all + wave * 16 * kScr, none);
+  float mu = 0.0f, rs = 1.0f;
+  if constexpr (has_norm<EPI>()) {
+    if (SW == 1 || w == 1) row_norm(a, mt, mu, rs);
+    if (SW == 1 || w == 1)
+      if (SW > 1 && lane < 16) norm_sh[lane] = make_float2(mu, rs);
+  }
+  if constexpr (SW > 1) {
+    if (w > 0)
+#pragma unroll
+      for (int j = 0; j < JT; ++j) red[w - 1][j][lane] = acc[j];
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int x = 0; x < SW - 1; ++x)
+#pragma unroll
+      for (int j = 0; j < JT; ++j) acc[j] += red[x][j][lane];
+    if constexpr (has_norm<EPI>()) {
+      mu = norm_sh[lane & 15].x;
+      rs = norm_sh[lane & 15].y;
+    }
+  }
+  epilogue_apply<EPI, JT>(a, t, mt, acc, scr_all + (SW == 1 ? wave : 0) * 16 * kScr, in, mu, rs);
+}
+
+// 4 waves a (tile, row tile) from 4 splits on, 1 below
+template <int EPI>
+hipError_t launch_epi_kernel(const GemmArgs& a, hipStream_t s, hipEvent_t stop) {
+  const unsigned units = (unsigned)(a.n_tiles * a.MT);
+  if (a.splits >= 4)
+    hipExtLaunchKernelGGL((gemm_epi_kernel<EPI, 4>), dim3(units), dim3(256), 0, s, nullptr, stop, 0, a);
+  else
+    hipExtLaunchKernelGGL((gemm_epi_kernel<EPI, 1>), dim3((units + 3) / 4), dim3(256), 0, s, nullptr, stop, 0, a);
+  return hipGetLastError();
 }
 
 template <int MT, int NW, int EPI>
@@ -1107,8 +1204,7 @@ hipError_t launch_rows(const GemmArgs& a, hipStream_t s, LaunchEvents ev) {
   if (two) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipExtLaunchKernelGGL((gemm_epi_kernel<MT, EPI>), dim3((a.n_tiles * MT + 3) / 4), dim3(256), 0, s, nullptr,
-                          ev.stop, 0, a);
+    return launch_epi_kernel<EPI>(a, s, ev.stop);
   }
   return hipGetLastError();
 }
@@ -1117,6 +1213,14 @@ template <int MT, int NW, int EPI, int JT>
 hipError_t launch_cfg(const GemmArgs& a, hipStream_t s, LaunchEvents ev) {
   hipExtLaunchKernelGGL((gemm_kernel<MT, NW, EPI, JT>), dim3(a.n_tiles * a.splits),
                         dim3(64 * block_waves<MT, NW, EPI>()), 0, s, ev.start, ev.stop, 0, a);
+  return hipGetLastError();
+}
+
+template <int MT, int EPI>
+hipError_t launch_groups(const GemmArgs& a, hipStream_t s, LaunchEvents ev) {
+  if (a.splits != 1 || a.row_groups > a.MT) return hipErrorInvalidValue;
+  hipExtLaunchKernelGGL((gemm_kernel<MT, 8, EPI, 4, true>), dim3((a.n_tiles + 7) / 8 * 8 * a.row_groups),
+                        dim3(64 * block_waves<MT, 8, EPI>()), 0, s, ev.start, ev.stop, 0, a);
   return hipGetLastError();
 }
 
@@ -1147,12 +1251,24 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t s, LaunchEvents ev) {
     }
   }
   if (a.jt != 4) return hipErrorInvalidValue;
+  if (a.row_groups > 0) {
+    switch ((a.MT + a.row_groups - 1) / a.row_groups) {
+      case 1: return launch_groups<1, EPI>(a, s, ev);
+      case 2: return launch_groups<2, EPI>(a, s, ev);
+      case 3: return launch_groups<3, EPI>(a, s, ev);
+      default: return hipErrorInvalidValue;
+    }
+  }
   if (a.wg_tiles > 1) {  // tiles per workgroup, the activation shared through LDS
     if (a.wg_tiles != 4) return hipErrorInvalidValue;
     switch (a.MT) {
       case 2: return launch_rows<2, 4, EPI>(a, s, ev);
       case 3: return launch_rows<3, 4, EPI>(a, s, ev);
+      case 4: return launch_rows<4, 4, EPI>(a, s, ev);
       case 5: return launch_rows<5, 4, EPI>(a, s, ev);
+      case 6: return launch_rows<6, 4, EPI>(a, s, ev);
+      case 7: return launch_rows<7, 4, EPI>(a, s, ev);
+      case 8: return launch_rows<8, 4, EPI>(a, s, ev);
       case 9: return launch_rows<9, 4, EPI>(a, s, ev);
       default: return hipErrorInvalidValue;
     }
@@ -1161,8 +1277,6 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t s, LaunchEvents ev) {
     case 1: return a.waves == 8 ? launch_cfg<1, 8, EPI, 4>(a, s, ev) : launch_cfg<1, 4, EPI, 4>(a, s, ev);
     case 2: return launch_cfg<2, 4, EPI, 4>(a, s, ev);
     case 3: return launch_cfg<3, 4, EPI, 4>(a, s, ev);
-    case 5: return launch_cfg<5, 4, EPI, 4>(a, s, ev);
-    case 9: return launch_cfg<9, 4, EPI, 4>(a, s, ev);
     default: return hipErrorInvalidValue;
   }
 }

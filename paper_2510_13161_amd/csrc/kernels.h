@@ -53,7 +53,8 @@ struct GemmArgs {
   const uint16_t* a_img;   // input image [K/32][MT][2][64][8]
   int32_t M, MT, K, N;     // N = logical output columns (padding masked)
   int32_t n_tiles, splits, waves;
-  int32_t jt;              // 16-column sub-tiles per tile: 4 (64 columns), 8 (128
+  int32_t jt;              // 16-column sub-tiles per tile: 4 (64 columns; with wg_tiles
+                           // 1 and no row groups up to 3 row tiles), 8 (128
                            // columns: EPI_SWIGLU with up to 3 row tiles and 2 waves,
                            // EPI_HEAD with one row tile and 4 waves) or 2 (32 columns:
                            // EPI_QKV with one row tile and 8 waves)
@@ -62,6 +63,8 @@ struct GemmArgs {
                            // activation through LDS; then waves = 4, and with
                            // splits > 1 a second kernel sums the splits and runs
                            // the epilogue)
+  int32_t row_groups;      // > 0: the row tiles in that many groups of at most 3, a
+                           // workgroup each (64-column tiles of 8 waves, splits = 1)
   int32_t map;
   const uint16_t* w0;
   const uint16_t* w1;

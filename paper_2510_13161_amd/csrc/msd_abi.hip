@@ -76,12 +76,11 @@ inline const uint16_t* head_w(const msd_model* m) {
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Row tiles of the kernels for M rows: 1, 2 or 3, else 5 (up to 80 rows),
-// else the 9-tile variant.
-inline int row_tiles(int M) {
-  const int mt = (M + 15) / 16;
-  return mt <= 3 ? mt : (mt <= 5 ? 5 : kMaxMT);
-}
+// 16-row tiles of M rows (1 .. kMaxMT). From 4 on every product of a padding
+// tile would be matrix-core time and power that the rows in use lack: at 7
+// tiles instead of 9 (99 rows) the 14B gate+up takes 100 -> 82 us, at 4
+// instead of 5 (63 rows) 72 -> 63.
+inline int row_tiles(int M) { return (M + 15) / 16; }
 
 // Split-K factor. A workgroup streams its 1/s of a tile at about one
 // compute unit's rate, so a GEMM lasts as long as its busiest unit: W =
@@ -123,14 +122,17 @@ int splits_for(const msd_model* m, int n_tiles, int K, int waves, int per_cu) {
 // ceil(n_tiles / 4) * s workgroups over the units within one dispatch
 // round, at most m->rows_max_splits (each split adds an fp32 partial of the
 // whole [M][64] tile to write and read back) and at least 8 k-steps a
-// split. Returns 0 where no split count balances at least 3/4 of the units
-// (then the split-K kernel runs), unless the kernel is forced. Measured:
+// split. Returns 0 where at 3 row tiles no split count balances at least 3/4
+// of the units (then the split-K kernel runs), unless the kernel is forced;
+// from 4 row tiles on sharing the activation gains more than the balance (66B
+// FFN up, 144 workgroup tiles, whole K: 215 -> 165 us at 80 rows, 342 -> 229
+// at 144). Measured:
 // 14B batch 16, FFN up (108 workgroup tiles, 2 splits) and LM head (594,
 // whole K): 136.8 -> 97.0 us and 740 -> 522 us; 66B tree (3 row tiles, one
 // workgroup a unit then): QKV (108, 2 splits) 118.3 -> 97.2 us, LM head
 // (197) 224.8 -> 166.5 us, its FFN up (144 workgroup tiles: 0.56 at best)
 // 168.8 -> 177.7 us.
-int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu) {
+int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu, bool lean) {
   const int64_t C = m->n_cus;
   const int64_t wg = (n_tiles + 3) / 4;
   const int max_s = std::max(1, std::min(m->rows_max_splits, (K / 32) / 8));
@@ -145,24 +147,24 @@ int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu) {
       best_bal = bal;
     }
   }
-  if (m->rows_forced) return best;
-  return best_bal >= 0.75 ? best : 0;
+  if (best_bal >= 0.75 || m->rows_forced) return best;
+  return per_cu > 1 ? 0 : (lean ? 1 : best);
 }
 
 // Narrow GEMMs (fewer tiles than m->rows_min_tiles) from 3 row tiles on:
 // the same kernel with many splits of K, so that the 144-row MFMA work
 // spreads over the chip, and the split sum plus epilogue in a kernel of its
-// own (one wave per row tile) instead of in the last split to arrive; the
-// split count as above, at most kRowsNarrowSplits, for matrices of at least
-// kRowsNarrowMinWeights weights (each split writes and the epilogue kernel
-// reads an fp32 partial of all M rows: 35 MB at 12 splits of a 5120-column
-// output). m->rows_narrow: 0 off, 1 that rule, 2 any size (tests). Measured at 14B batch 16 (µs, GEMM +
-// epilogue kernel against the split-K kernel): QKV 32.6 + 13.6 against
-// 51.7, FFN down 43.8 + 10.2 against 66.4, but the O projection (26M
-// weights, 13 k-steps a split) 34.0 + 10.5 against 36.3; 66B tree (3 row
-// tiles, two workgroups a unit, 7 splits, 12 MB of partials): O 46.4 ->
-// 31.5 + 7.3, down 154.2 -> 116.9 + 7.3, 30.0 -> 28.1 ms per step; at 2
-// row tiles (14B tree) slower, 8.41 -> 8.78 ms.
+// own (gemm_epi_kernel) instead of in the last split to arrive; the split
+// count as above, at most kRowsNarrowSplits. m->rows_narrow: 0 off, 1 at 3
+// row tiles for matrices of at least kRowsNarrowMinWeights weights (each
+// split writes and the epilogue kernel reads an fp32 partial of all M rows)
+// and from 4 row tiles for all that row groups (below) leave, 2 any size
+// (tests). Measured against the split-K kernel's last-arrival epilogue (us,
+// both kernels): 14B at 144 rows QKV 51.7 -> 43, O 35.5 -> 29.8, FFN down 66.4
+// -> 50; 99 rows O 34.6 -> 27.1; at 3 row tiles O (26M weights, 36 rows) 20.8
+// against 19.5, so not there; 66B tree (3 row tiles, two workgroups a unit, 7
+// splits) O 46.4 -> 37.4, down 154.2 -> 121; at 2 row tiles slower (14B tree,
+// QKV 24.3 against 22.4).
 constexpr int kRowsNarrowSplits = 16;
 constexpr int64_t kRowsNarrowMinWeights = 32ll << 20;
 int rows_narrow_splits(const msd_model* m, int n_tiles, int K, int per_cu) {
@@ -186,21 +188,46 @@ int rows_narrow_splits(const msd_model* m, int n_tiles, int K, int per_cu) {
 struct GemmShape {
   int n_tiles, K, splits, waves, jt;
   int wg_tiles = 1;
+  int row_groups = 0;
 };
 
 struct Shapes {
   GemmShape qkv, o, up, down, head;
 };
 
+// Small matrices at several row tiles (fewer than m->rows_min_tiles 64-column
+// tiles): the row tiles in groups of at most 3, whole K, as many groups as fit
+// the compute units. Split-K and the LDS-shared kernel spend their time there on
+// partials and hand-offs (0.6B-shaped layer at 72 rows: 18 us a GEMM, 11.5 in
+// groups). The line by weights: from 4 row tiles 24M (21M weights in 64 tiles
+// at 144 rows 32.5 us against 36.5 in the LDS-shared kernel with 16 splits, 63
+// rows 25.1 against 27.0; 26M in 80 tiles 30.9 against 29.7 and 26.6 against
+// 23.7), at 2 and 3 row tiles 8M (6M: 10.7 against 12.8 us; 21M: 25.5 against
+// 17.3), and there not the residual projections, whose K is the longer one
+// and whose split-K hand-off is a single row tile a wave (3M at 2 row tiles:
+// 15.1 against 12.4).
+constexpr int64_t kGroupMaxWeights = 24ll << 20, kGroupMaxWeightsFewRows = 8ll << 20;
+int row_groups(const msd_model* m, int n_tiles, int mt) {
+  return std::min(mt, std::max((mt + 2) / 3, m->n_cus / n_tiles));
+}
+
 // Tiles and waves per workgroup. With one row tile, a GEMM with fewer
 // 64-column tiles than the workgroup target runs split-K workgroups of
 // m->waves (8) waves, one with more (the LM head) whole-K workgroups of 4
-// waves. Several row tiles: 64-column tiles, 4 waves. The SwiGLU FFN up
-// projection with up to 3 row tiles: whole-K 128-column tiles of 2 waves
-// (216 workgroups at the 14B shape, one dispatch round: at most one per CU).
-Shapes shapes(const msd_model* m, int M) {
+// waves; 2 and 3 row tiles 64-column tiles of 4 waves, unless in row groups or in
+// the kernel that shares the activation through LDS; from 4 row tiles on one of
+// these two. The SwiGLU FFN up projection with up to 3 row tiles: whole-K
+// 128-column tiles of 2 waves (216 workgroups at the 14B shape, one dispatch
+// round: at most one per CU), at one row tile only where its 64-column tiles
+// do not fit the compute units (else split-K tiles of 8 waves: 6M weights 10.4
+// -> 8.8 us), at 3 only where the LDS-shared kernel does not balance (14B, 36
+// rows: 63 -> 59 us there).
+// lean: the shapes of the smallest workspace (no split partials where row
+// groups or whole K can stand in), for blocks that then fit the static scratch.
+Shapes shapes(const msd_model* m, int M, bool lean) {
   const msd_model_config& c = m->cfg;
-  const bool one = row_tiles(M) == 1;
+  const int mt = row_tiles(M);
+  const bool one = mt == 1;
   Shapes s;
   s.qkv.n_tiles = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim / kTileN;
   s.qkv.K = c.d_model;
@@ -216,11 +243,6 @@ Shapes shapes(const msd_model* m, int M) {
     g->jt = 4;
     g->waves = one && g->n_tiles < m->n_cus ? m->waves : 4;
   }
-  if (row_tiles(M) <= 3 && c.act == MSD_ACT_SWIGLU && c.d_ffn % 64 == 0) {
-    s.up.jt = 8;
-    s.up.n_tiles = c.d_ffn / 64;
-    s.up.waves = 2;
-  }
   // The QKV projection at one row tile, where twice its 64-column tile count
   // still fits the compute units: 32-column tiles (16 rotary pairs of a head)
   // of 8 waves, whole K (no split hand-off), 224 workgroups at the 14B
@@ -231,32 +253,57 @@ Shapes shapes(const msd_model* m, int M) {
     s.qkv.n_tiles = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim / 32;
     s.qkv.waves = 8;
   }
-  if (one) {  // the LM head at one row tile: 128-column tiles of 4 waves
+  // the LM head at one row tile: 128-column tiles of 4 waves, unless its
+  // 64-column tiles fit the compute units (split-K tiles of 8 waves as the
+  // projections': 4096 x 5120 weights 36.7 -> 16.3 us, 4096 x 1024 14.1 -> 9.5)
+  if (one && (lean || s.head.n_tiles >= m->n_cus)) {
     s.head.jt = 8;
     s.head.n_tiles = (c.vocab + 2 * kTileN - 1) / (2 * kTileN);
     s.head.waves = 4;
   }
   for (GemmShape* g : {&s.qkv, &s.o, &s.up, &s.down, &s.head}) {
-    const int rs = row_tiles(M) >= m->rows_min_mt && g->n_tiles >= m->rows_min_tiles && g->jt == 4
-                       ? rows_splits(m, g->n_tiles, g->K, row_tiles(M) <= 3 ? 2 : 1)
-                       : 0;
-    if (rs > 0) {  // 4 tiles a workgroup, the activation shared in LDS
+    const int64_t weights = (int64_t)g->n_tiles * kTileN * g->K;
+    const bool wide = g->n_tiles >= m->rows_min_tiles, resid = g == &s.o || g == &s.down;
+    const int per_cu = mt <= 3 ? 2 : 1;
+    if (!one && !wide && m->rows_narrow == 1 &&
+        (mt >= 4 ? weights <= (lean ? kRowsNarrowMinWeights - 1 : kGroupMaxWeights)
+                 : weights <= kGroupMaxWeightsFewRows && !resid)) {
+      g->row_groups = row_groups(m, g->n_tiles, mt);
+      g->waves = 8;
+      g->splits = 1;
+      continue;
+    }
+    int rs = 0;  // splits of the LDS-shared kernel (4 tiles a workgroup); 0: not taken
+    const bool pair_up = g == &s.up && c.act == MSD_ACT_SWIGLU && mt <= 3 && !(one && g->n_tiles <= m->n_cus);
+    if (g->jt == 4 && wide && mt >= m->rows_min_mt && !(lean && pair_up))
+      rs = rows_splits(m, g->n_tiles, g->K, per_cu, lean);
+    else if (g->jt == 4 && !wide && !pair_up && mt >= m->rows_narrow_mt &&
+             (m->rows_narrow == 2 || (m->rows_narrow == 1 && (mt >= 4 || weights >= kRowsNarrowMinWeights))))
+      rs = rows_narrow_splits(m, g->n_tiles, g->K, per_cu);
+    if (rs > 0) {
       g->wg_tiles = 4;
       g->waves = 4;
       g->splits = rs;
-    } else if (m->rows_narrow && row_tiles(M) >= m->rows_narrow_mt && g->jt == 4 && g->n_tiles < m->rows_min_tiles &&
-               (m->rows_narrow == 2 || (int64_t)g->n_tiles * kTileN * g->K >= kRowsNarrowMinWeights)) {
-      g->wg_tiles = 4;
-      g->waves = 4;
-      g->splits = rows_narrow_splits(m, g->n_tiles, g->K, row_tiles(M) <= 3 ? 2 : 1);
-    } else {
-      g->splits = splits_for(m, g->n_tiles, g->K, g->waves, g->waves >= 8 ? 1 : 2);
+      continue;
     }
+    if (mt >= 4) {  // the LDS-shared kernel switched off
+      g->row_groups = row_groups(m, g->n_tiles, mt);
+      g->waves = 8;
+      g->splits = 1;
+      continue;
+    }
+    if (pair_up) {
+      g->jt = 8;
+      g->n_tiles = c.d_ffn / 64;
+      g->waves = 2;
+    }
+    g->splits = splits_for(m, g->n_tiles, g->K, g->waves, g->waves >= 8 ? 1 : 2);
   }
   return s;
 }
 
 struct Layout {
+  Shapes s;
   size_t x, stats, q, img_x, img_h, img_f, img_attn, img_act, partial, counters, part_o, part_ml,
       tile_ms, tile_top, head_ms, head_top, total;
   int64_t n_counters, n_gemm_counters;
@@ -266,13 +313,13 @@ struct Layout {
 // image bytes of an [M][K] activation
 inline size_t img_bytes(int K, int MT) { return (size_t)(K / 32) * MT * 1024 * sizeof(uint16_t); }
 
-Layout layout(const msd_model* m, int batch, int n_slots, int kappa, int capacity) {
+Layout layout_of(const msd_model* m, const Shapes& s, int batch, int n_slots, int kappa, int capacity) {
   const msd_model_config& c = m->cfg;
   const int M = batch * n_slots;
-  const Shapes s = shapes(m, M);
   const int kmax = kappa > 1 ? kappa : 1;
   const int qd = c.n_heads * c.head_dim;
   Layout L{};
+  L.s = s;
   L.MT = row_tiles(M);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -300,7 +347,6 @@ Layout layout(const msd_model* m, int batch, int n_slots, int kappa, int capacit
       max_tiles = g->n_tiles > max_tiles ? g->n_tiles : max_tiles;
     }
   }
-  L.partial = take(part);
   // the GEMMs' split-K counters, then the attention's chunk counters (one per
   // sequence, kv head and query tile); all cleared by the rows kernel
   const int attn_qt = ((c.n_heads / c.n_kv_heads) * n_slots + 15) / 16;
@@ -310,8 +356,16 @@ Layout layout(const msd_model* m, int batch, int n_slots, int kappa, int capacit
   L.max_chunks = (capacity + kAttnChunk - 1) / kAttnChunk;
   const size_t qn = (size_t)(c.n_heads / c.n_kv_heads) * n_slots;
   const size_t nparts = (size_t)batch * c.n_kv_heads * L.max_chunks * qn;
+  // the GEMMs' and the attention's partials share one region: a GEMM's are read
+  // by its own last kernel, the attention's by its own, and every kernel of a
+  // step runs after the one before it
+  const size_t shared = off;
+  L.partial = take(part);
+  const size_t gemm_end = off;
+  off = shared;
   L.part_o = take(nparts * c.head_dim * sizeof(float));
   L.part_ml = take(nparts * sizeof(float2));
+  off = std::max(off, gemm_end);
   L.tile_ms = take((size_t)s.head.n_tiles * M * sizeof(float2));
   L.tile_top = take((size_t)s.head.n_tiles * M * kmax * sizeof(uint64_t));
   const int parts = head_parts(s.head.n_tiles);
@@ -319,6 +373,16 @@ Layout layout(const msd_model* m, int batch, int n_slots, int kappa, int capacit
   L.head_top = take((size_t)parts * M * kmax * sizeof(uint64_t));
   L.total = off;
   return L;
+}
+
+// the workspace layout of a block and the GEMM shapes it is for: the lean ones
+// where only they fit the static scratch
+Layout layout(const msd_model* m, int batch, int n_slots, int kappa, int capacity) {
+  const int M = batch * n_slots;
+  const Layout L = layout_of(m, shapes(m, M, false), batch, n_slots, kappa, capacity);
+  if (L.total <= kStaticScratchBytes) return L;
+  const Layout lean = layout_of(m, shapes(m, M, true), batch, n_slots, kappa, capacity);
+  return lean.total <= kStaticScratchBytes ? lean : L;
 }
 
 msd_status make_topo(const msd_block* blk, Topo* topo) {
@@ -422,6 +486,7 @@ GemmArgs gemm_base(const msd_model* m, const Layout& L, char* ws, int M, const G
   g.waves = sh.waves;
   g.jt = sh.jt;
   g.wg_tiles = sh.wg_tiles;
+  g.row_groups = sh.row_groups;
   g.partial = reinterpret_cast<float*>(ws + L.partial);
   g.counters = reinterpret_cast<int32_t*>(ws + L.counters);
   g.n_heads = m->cfg.n_heads;
@@ -853,7 +918,7 @@ msd_status verify_launch(const msd_model* m, msd_kv_cache* kv, const msd_block* 
   msd_status st = MSD_OK;
   const msd_model_config& c = m->cfg;
   const int M = blk->batch * blk->n_slots;
-  const Shapes s = shapes(m, M);
+  const Shapes& s = L.s;
   const int d = c.d_model, qd = c.n_heads * c.head_dim;
   float* x = reinterpret_cast<float*>(w + L.x);
   float2* stats = reinterpret_cast<float2*>(w + L.stats);
@@ -1009,7 +1074,7 @@ msd_status msd_early_exit_topk(const msd_model* m, const float* hidden, int32_t 
   if (!aligned16(hidden)) return fail(MSD_ERR_INVALID_ARG, "hidden must be 16-byte aligned");
   const Layout L = layout(m, 1, M, kappa, 1);
   if (!ws || ws_bytes < L.total) return fail(MSD_ERR_WORKSPACE, "workspace too small");
-  const Shapes s = shapes(m, M);
+  const Shapes& s = L.s;
   char* w = static_cast<char*>(ws);
   float2* stats = reinterpret_cast<float2*>(w + L.stats);
   // statistics and final-norm image of the given rows; clears the head
