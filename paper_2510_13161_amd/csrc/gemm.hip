@@ -1002,14 +1002,26 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
         slot_in = slot_in + 1 == R ? 0 : slot_in + 1;
       }
     }
+    // with splits of K the epilogue kernel takes the rows' norms from memory:
+    // the loaders of the first MT workgroups merge them, a row tile each, while
+    // their compute waves store the partials
+    if constexpr (has_norm<EPI>()) {
+      if (a.splits > 1 && a.norm_rows) {
+        for (int mt = blockIdx.x; mt < MT; mt += gridDim.x) {
+          float mu, rs;
+          row_norm(a, mt, mu, rs);
+          if (lane < 16 && 16 * mt + lane < a.M) a.norm_rows[16 * mt + lane] = make_float2(mu, rs);
+        }
+      }
+    }
     return;
   }
 
-  // the pre-norm's (mu, r) of every row, merged once before the k-loop (the
-  // summaries' registers are free then) and left in LDS for the epilogues;
-  // barrier 0 below orders the writes before any read
+  // whole K: the pre-norm's (mu, r) of every row, merged once before the
+  // k-loop (the summaries' registers are free then) and left in LDS for the
+  // epilogues; barrier 0 below orders the writes before any read
   if constexpr (has_norm<EPI>()) {
-    for (int mt = wave; mt < MT; mt += NW) {
+    for (int mt = wave; mt < MT && a.splits == 1; mt += NW) {
       float mu, rs;
       row_norm(a, mt, mu, rs);
       if (lane < 16) norm_sh[16 * mt + lane] = make_float2(mu, rs);
@@ -1123,15 +1135,18 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
 // MFMA work of 144 rows). A (64-column tile, row tile) belongs to SW waves:
 // wave w sums the partials of splits w, w + SW, .. (all its loads in flight at
 // once), wave 0 joins the waves' sums in wave order and runs the epilogue,
-// whose other inputs it loaded meanwhile, and with SW = 4 wave 1 merges the
-// row norms.
+// whose other inputs (the rows' norms from a.norm_rows) it loaded meanwhile.
+// Bound by its chain of loads and by instruction issue, not by bytes: at 144
+// rows one wave a unit that merged the row norms itself and took its splits
+// 4 at a time in series was 15.3 us for the 14B gate+up, 13.6 for QKV, 10.3
+// for O and down (8.4 at 36 rows); the sum over 4 waves takes O and down to 9.8 (5.5), the norms from memory
+// the gate+up pair (both kernels) from 104 to 96-101, QKV's from 42.3 to 37.4.
 template <int EPI, int SW>
-__global__ __launch_bounds__(256) void gemm_epi_kernel(GemmArgs a) {
+__global__ __launch_bounds__(256, EPI == EPI_RESID ? 3 : 4) void gemm_epi_kernel(GemmArgs a) {
   constexpr int JT = 4;
-  constexpr int SB = 4;  // partials in flight per wave
+  constexpr int SB = SW == 1 ? 3 : 4;  // partials in flight per wave
   __shared__ __attribute__((aligned(16))) float scr_all[(4 / SW) * 16 * kScr];
   __shared__ floatx4 red[SW > 1 ? SW - 1 : 1][JT][kWave];
-  __shared__ float2 norm_sh[16];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int u = SW == 1 ? blockIdx.x * 4 + wave : blockIdx.x, w = SW == 1 ? 0 : wave;
@@ -1141,6 +1156,11 @@ __global__ __launch_bounds__(256) void gemm_epi_kernel(GemmArgs a) {
   const float* part = a.partial + (size_t)t * a.splits * TF + mt * JT * 256 + lane * 4;
   EpiIn in;
   if constexpr (EPI == EPI_QKV) in.L = row_len(a, 16 * mt + (lane & 15));
+  float2 norm = make_float2(0.0f, 1.0f);
+  if constexpr (has_norm<EPI>()) {
+    const int m = 16 * mt + (lane & 15);
+    norm = a.norm_rows[m < a.M ? m : 0];
+  }
   floatx4 acc[JT];
 #pragma unroll
   for (int j = 0; j < JT; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1148,10 +1168,10 @@ __global__ __launch_bounds__(256) void gemm_epi_kernel(GemmArgs a) {
     floatx4 pv[SB][JT];
 #pragma unroll
     for (int q = 0; q < SB; ++q) {
-      const int sp = s0 + q * SW < a.splits ? s0 + q * SW : s0;
+      if (s0 + q * SW >= a.splits) continue;
 #pragma unroll
       for (int j = 0; j < JT; ++j)
-        pv[q][j] = *reinterpret_cast<const floatx4*>(part + sp * TF + j * 256);
+        pv[q][j] = *reinterpret_cast<const floatx4*>(part + (s0 + q * SW) * TF + j * 256);
     }
     if (s0 == 0) epi_load<EPI, false, JT>(a, t, mt, in);
 #pragma unroll
@@ -1159,12 +1179,6 @@ __global__ __launch_bounds__(256) void gemm_epi_kernel(GemmArgs a) {
       if (s0 + q * SW < a.splits)
 #pragma unroll
         for (int j = 0; j < JT; ++j) acc[j] += pv[q][j];
-  }
-  float mu = 0.0f, rs = 1.0f;
-  if constexpr (has_norm<EPI>()) {
-    if (SW == 1 || w == 1) row_norm(a, mt, mu, rs);
-    if (SW == 1 || w == 1)
-      if (SW > 1 && lane < 16) norm_sh[lane] = make_float2(mu, rs);
   }
   if constexpr (SW > 1) {
     if (w > 0)
@@ -1176,12 +1190,8 @@ __global__ __launch_bounds__(256) void gemm_epi_kernel(GemmArgs a) {
     for (int x = 0; x < SW - 1; ++x)
 #pragma unroll
       for (int j = 0; j < JT; ++j) acc[j] += red[x][j][lane];
-    if constexpr (has_norm<EPI>()) {
-      mu = norm_sh[lane & 15].x;
-      rs = norm_sh[lane & 15].y;
-    }
   }
-  epilogue_apply<EPI, JT>(a, t, mt, acc, scr_all + (SW == 1 ? wave : 0) * 16 * kScr, in, mu, rs);
+  epilogue_apply<EPI, JT>(a, t, mt, acc, scr_all + (SW == 1 ? wave : 0) * 16 * kScr, in, norm.x, norm.y);
 }
 
 // 4 waves a (tile, row tile) from 4 splits on, 1 below

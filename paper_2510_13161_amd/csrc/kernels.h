@@ -73,6 +73,7 @@ struct GemmArgs {
   float* partial;          // [n_tiles][splits][MT * jt * 256] (splits > 1)
   int32_t* counters;       // [n_tiles], zero on entry, left zero on exit
   RowNorm norm;
+  float2* norm_rows;       // [M] (mu, r), from gemm_rows_kernel to its epilogue kernel
   const uint16_t* b0;      // bias of w0 (q / plain / up)
   const uint16_t* b1;      // bias of w1 (k)
   const uint16_t* b2;      // bias of w2 (v)

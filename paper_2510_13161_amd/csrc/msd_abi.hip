@@ -489,6 +489,9 @@ GemmArgs gemm_base(const msd_model* m, const Layout& L, char* ws, int M, const G
   g.row_groups = sh.row_groups;
   g.partial = reinterpret_cast<float*>(ws + L.partial);
   g.counters = reinterpret_cast<int32_t*>(ws + L.counters);
+  // the rows' norms between a GEMM and its epilogue kernel ([M], at most the
+  // head's first-stage results, which are written after any GEMM)
+  g.norm_rows = reinterpret_cast<float2*>(ws + L.head_ms);
   g.n_heads = m->cfg.n_heads;
   g.n_kv_heads = m->cfg.n_kv_heads;
   g.head_dim = m->cfg.head_dim;
