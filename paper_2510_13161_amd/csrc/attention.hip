@@ -709,8 +709,73 @@ __global__ __launch_bounds__(256, 1) void attn_stream_kernel(AttnArgs a) {
                    qt0 + ntile, Qn, nch, pbase, pco);
 }
 
+// 64-key blocks of sequence b; none past the capacity (flagged, left out)
+__device__ __forceinline__ int attn_blocks(const AttnArgs& a, int b) {
+  const int T = a.len[b] + a.n_slots;
+  return T > a.capacity || T < 1 ? 0 : (T + 63) >> 6;
+}
+
+// The ring kernel's chunks are of a.chunk_blocks blocks, or, where that is 0, of
+// a length that the device takes from the sequences' lengths. One sequence:
+// equal shares of its workgroups.
+constexpr int kMinChunkBlocks = kAttnChunk / 64;  // at most max_chunks chunks a sequence
+__device__ __forceinline__ int attn_chunk(const AttnArgs& a, int n) {
+  return a.chunk_blocks > 0 ? a.chunk_blocks : max(kMinChunkBlocks, (n + a.wgs - 1) / a.wgs);
+}
+
+// Several: every sequence in chunks of G blocks, G the smallest of 64 candidates (from kMinChunkBlocks and an equal share up to
+// one chunk a sequence) at which all chunks fit a.wgs workgroups, so that one
+// round of workgroups ends together whatever the lengths, which only the
+// device knows. One wave counts: G, and into chunk0[b] (b <= batch) the
+// chunks of the sequences before b.
+__device__ __forceinline__ int attn_plan(const AttnArgs& a, int* chunk0) {
+  const int lane = threadIdx.x & 63;
+  const int n0 = lane < a.batch ? attn_blocks(a, lane) : 0;  // sequences 0 .. 63
+  auto blocks = [&](int b) { return b < 64 ? n0 : (b < a.batch ? attn_blocks(a, b) : 0); };
+  int total = 0, most = 0;
+  for (int b0 = 0; b0 < a.batch; b0 += 64) {
+    int t = blocks(b0 + lane), m = t;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      t += __shfl_xor(t, o);
+      m = max(m, __shfl_xor(m, o));
+    }
+    total += t;
+    most = max(most, m);
+  }
+  const int lo = max(kMinChunkBlocks, (total + a.wgs - 1) / a.wgs);
+  const int step = max(1, (most - lo + 62) / 63);
+  const int g = lo + lane * step;  // the last is >= most: one chunk a sequence
+  const float inv = 1.0f / (float)g;
+  int chunks = 0;
+  for (int b0 = 0; b0 < a.batch; b0 += 64) {
+    const int nb = blocks(b0 + lane);
+    for (int i = 0; i < 64 && b0 + i < a.batch; ++i) {
+      // ceil(n / g): exact, as (n - 1/2) / g lies at least 1 / (2 g) from any integer
+      const int n = __builtin_amdgcn_readlane(nb, i);
+      chunks += n > 0 ? (int)(((float)n - 0.5f) * inv) + 1 : 0;
+    }
+  }
+  const unsigned long long fit = __ballot(chunks <= a.wgs);
+  const int G = lo + step * (fit ? __ffsll((long long)fit) - 1 : 63);
+  int before = 0;
+  for (int b0 = 0; b0 < a.batch; b0 += 64) {
+    const int b = b0 + lane, n = (blocks(b) + G - 1) / G;
+    int x = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    if (b < a.batch) chunk0[b] = before + x - n;
+    before += __shfl(x, 63);
+  }
+  if (lane == 0) chunk0[a.batch] = before;
+  return G;
+}
+
 // Long contexts, fed through an LDS ring (head dim 128): a workgroup owns
-// a chunk of nb consecutive 256-key spans of one (sequence, kv head) and a
+// a chunk of consecutive 64-key blocks of one (sequence, kv head) and a
 // group of up to 4 query tiles, two compute waves per tile (one per 32-key
 // half of every block, so that each SIMD holds two and one's softmax overlaps
 // the other's MFMAs; the two halves are merged once at the end). Two loader waves
@@ -751,6 +816,7 @@ __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a
   __shared__ __attribute__((aligned(16))) uint16_t ring[R][2][64 * HD];
   __shared__ float2 ml_sh[NQ][2][16];
   __shared__ int last;
+  __shared__ int plan_sh[kMaxAttnBatch + 2];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -760,18 +826,45 @@ __global__ __launch_bounds__(64 * (2 * NQ + 2)) void attn_ring_kernel(AttnArgs a
   const int Qn = G * ns;
   const int QT = (Qn + 15) >> 4;
   const int QG = (QT + NQ - 1) / NQ;
-  const AttnWg wg = attn_wg(a, (a.max_chunks + a.nb - 1) / a.nb, QG);
-  const int b = wg.b, kvh = wg.kvh, qgi = wg.qgi, c = wg.c;
+  // kv head first, as attn_wg: workgroup w of the kv head's a.wgs takes the
+  // plan's chunk w
+  const int kvh = blockIdx.x % a.n_kv_heads, w = blockIdx.x / a.n_kv_heads % a.wgs;
+  const int qgi = blockIdx.x / a.n_kv_heads / a.wgs;
   const int qt0 = qgi * NQ, ntile = min(NQ, QT - qt0);
+  int b, c, nch, ck;  // sequence, chunk, its chunks, keys a chunk
+  if (a.chunk_blocks > 0 || a.batch == 1) {
+    const int per = a.wgs / a.batch;  // chunks of a sequence at most
+    b = w / per;
+    c = w - b * per;
+    if (b >= a.batch) return;
+    const int n = attn_blocks(a, b), G = attn_chunk(a, n);
+    nch = (n + G - 1) / G;
+    ck = 64 * G;
+    if (c >= nch) {
+      if (c == 0 && kvh == 0 && qgi == 0 && tid == 0 && a.len[b] + ns > a.capacity) atomicOr(a.status, 1u);
+      return;
+    }
+  } else {
+    if (wave == 0) {
+      const int G = attn_plan(a, plan_sh);
+      if (lane == 0) plan_sh[a.batch + 1] = G;
+    }
+    __syncthreads();
+    if (blockIdx.x == gridDim.x - 1)  // the workgroup most likely without a chunk
+      for (int i = tid; i < a.batch; i += blockDim.x)
+        if (a.len[i] + ns > a.capacity) atomicOr(a.status, 1u);
+    if (w >= plan_sh[a.batch]) return;
+    for (int b0 = 0;; b0 += 64) {
+      const unsigned long long past = __ballot(plan_sh[min(b0 + lane + 1, a.batch)] > w);
+      b = b0 + (past ? __ffsll((long long)past) - 1 : 0);
+      if (past) break;
+    }
+    c = __builtin_amdgcn_readfirstlane(w - plan_sh[b]);
+    nch = __builtin_amdgcn_readfirstlane(plan_sh[b + 1] - plan_sh[b]);
+    ck = 64 * __builtin_amdgcn_readfirstlane(plan_sh[a.batch + 1]);
+  }
   const int L = a.len[b];
   const int T = L + ns;
-  if (T > a.capacity) {
-    if (c == 0 && kvh == 0 && qgi == 0 && tid == 0) atomicOr(a.status, 1u);
-    return;
-  }
-  const int ck = a.nb * kAttnChunk;  // keys per chunk
-  const int nch = (T + ck - 1) / ck;
-  if (c >= nch) return;
   const int kbeg = c * ck;
   const int nblk = (min(T, kbeg + ck) - kbeg + 63) >> 6;
   const size_t row0 = ((size_t)b * a.n_kv_heads + kvh) * a.capacity;
@@ -1012,11 +1105,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   const int G = a.n_heads / a.n_kv_heads, ns = a.n_slots, Qn = G * ns;
   const int b = blockIdx.z, kvh = blockIdx.y;
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= Qn * C4) return;
   const int T = a.len[b] + ns;
   if (T > a.capacity) return;  // flagged by the attention kernel
-  const int nch = (T + a.nb * kAttnChunk - 1) / (a.nb * kAttnChunk);
-  if (nch <= 1) return;        // written by its only chunk
+  int nch = (T + a.nb * kAttnChunk - 1) / (a.nb * kAttnChunk);
+  if (a.ring && (a.chunk_blocks > 0 || a.batch == 1)) {
+    const int n = attn_blocks(a, b), G = attn_chunk(a, n);
+    nch = (n + G - 1) / G;
+  } else if (a.ring) {
+    __shared__ int plan_sh[kMaxAttnBatch + 1];
+    if (threadIdx.x < 64) attn_plan(a, plan_sh);
+    __syncthreads();
+    nch = plan_sh[b + 1] - plan_sh[b];
+  }
+  if (nch <= 1 || x >= Qn * C4) return;  // written by its only chunk
   const int qg = x / C4, c4 = x - qg * C4;
   const size_t pbase = ((size_t)b * a.n_kv_heads + kvh) * a.max_chunks;
   float M = -INFINITY, S = 0.0f, o4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -1061,7 +1162,12 @@ hipError_t launch_attention(int head_dim, const AttnArgs& a, hipStream_t s) {
   if (a.ring) {
     // the ring-fed kernel: head dim 128, up to 4 query tiles a workgroup
     if (head_dim != 128 || a.q_per_wg > 4) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((a.max_chunks + a.nb - 1) / a.nb) * a.n_kv_heads * qg * a.batch);
+    // (and a workgroup for every chunk: one a sequence always fits)
+    if (a.wgs < a.batch || a.batch > kMaxAttnBatch || (a.chunk_blocks != 0 && a.chunk_blocks < kAttnChunk / 64))
+      return hipErrorInvalidValue;
+    const int ck = a.chunk_blocks * 64;
+    if (ck > 0 && (int64_t)a.wgs < (int64_t)a.batch * ((a.capacity + ck - 1) / ck)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)a.wgs * a.n_kv_heads * qg);
     switch (a.q_per_wg) {
       case 1: hipLaunchKernelGGL((attn_ring_kernel<1>), grid, dim3(64 * 4), 0, s, a); break;
       case 2: hipLaunchKernelGGL((attn_ring_kernel<2>), grid, dim3(64 * 6), 0, s, a); break;

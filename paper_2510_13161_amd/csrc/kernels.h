@@ -148,6 +148,7 @@ hipError_t launch_rows(const RowsArgs& a, hipStream_t s);
 // ---------------------------------------------------------------------------
 constexpr int kMaxAttnChunks = 128;   // key chunks per (sequence, kv head)
 constexpr int kMaxCapacity = 32768;   // cache positions
+constexpr int kMaxAttnBatch = 16 * kMaxMT;  // sequences of a block: a row each at least
 constexpr int kAttnChunk = 256;       // keys per workgroup (4 waves x 64)
 
 struct AttnArgs {
@@ -170,8 +171,11 @@ struct AttnArgs {
   float scale;
   int32_t defer;            // 1: chunks only publish their partials; a second
                             // kernel merges them (no in-kernel hand-off)
-  int32_t ring;             // 1: attn_ring_kernel (head dim 128, chunks of nb spans,
-                            // q_per_wg <= 4 tiles a workgroup)
+  int32_t ring;             // 1: attn_ring_kernel (head dim 128, q_per_wg <= 4 tiles a
+                            // workgroup)
+  int32_t wgs;              // ring: workgroups per kv head and query group (>= batch)
+  int32_t chunk_blocks;     // ring: 64-key blocks a chunk, 0: from the lengths, so that
+                            // all chunks fit wgs
   Topo topo;
 };
 hipError_t launch_attention(int head_dim, const AttnArgs& a, hipStream_t s);

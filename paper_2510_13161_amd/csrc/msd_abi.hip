@@ -447,31 +447,44 @@ constexpr int64_t kAttnStreamWgs = 256;
 struct AttnShape {
   int q_per_wg, nb;
   bool ring;
+  int wgs, chunk_blocks;  // ring
 };
-// Chunks of several spans take attn_ring_kernel at head dim 128 (up to 4
-// query tiles a workgroup, K and V fed through an LDS ring; m->attn_ring 0
-// keeps attn_stream_kernel, up to 3 tiles).
+// At head dim 128 such grids take attn_ring_kernel (up to 4 query tiles a
+// workgroup, K and V fed through an LDS ring; m->attn_ring 0 keeps
+// attn_stream_kernel, up to 3 tiles). One sequence, or chunks of
+// kAttnPlanSpans spans or more: a workgroup per compute unit (the ring fills
+// its LDS) and chunks that the device sizes from the lengths, as chunks sized
+// for the capacity leave the units of short sequences idle while a long one's
+// run on (14B batch 16 at 512 to 8192: 85.9 -> 73.3 us; the tree's one
+// sequence at 4096: 14.3 -> 12.7). Below, counting costs what it gains (8 at
+// 1024, 2 spans: 16.1 against 17.0 us; 11 at 256 to 4096, 6 spans: 38.5
+// against 35.9). m->attn_spans > 0: chunks of that many spans.
+constexpr int kAttnPlanSpans = 6;
 AttnShape attn_shape(const msd_model* m, int max_chunks, int n_kv_heads, int batch, int q_tiles,
                      int head_dim) {
   const bool ring = m->attn_ring != 0 && head_dim == 128;
   const int qs = std::min(ring ? 4 : 3, q_tiles);
-  const int64_t grid1 = (int64_t)max_chunks * n_kv_heads * batch * ((q_tiles + qs - 1) / qs);
+  const int groups = (q_tiles + qs - 1) / qs;
+  const int64_t grid1 = (int64_t)max_chunks * n_kv_heads * batch * groups;
   int64_t nb = m->attn_spans > 0 ? m->attn_spans : (grid1 + kAttnStreamWgs - 1) / kAttnStreamWgs;
   nb = std::min<int64_t>(nb, max_chunks);
-  if (nb >= 2) return {qs, (int)nb, ring};
-  return {attn_q_per_wg(max_chunks, n_kv_heads, batch, q_tiles), 1, false};
+  if (nb < 2) return {attn_q_per_wg(max_chunks, n_kv_heads, batch, q_tiles), 1, false, 0, 0};
+  if (!ring) return {qs, (int)nb, false, 0, 0};
+  if (m->attn_spans <= 0 && (batch == 1 || nb >= kAttnPlanSpans))
+    return {qs, (int)nb, true, std::max(batch, m->n_cus / (n_kv_heads * groups)), 0};
+  return {qs, (int)nb, true, batch * (int)((max_chunks + nb - 1) / nb), (int)nb * (kAttnChunk / 64)};
 }
 
 // Chunk merge in a kernel of its own (instead of the last chunk to arrive)
-// from kAttnDeferChunks chunks of the cache's capacity on (m->attn_defer: -1
-// that rule, 0 never, 1 always). Measured: the 14B tree (9 chunks of 2
-// spans) 8.62 -> 8.30 ms per step; where the last-arrival merge is short
-// (the chain's 5 one-span chunks, 2 or 3 chunks at batch 16 and the 66B
-// tree) the extra launch does not pay.
+// from kAttnDeferChunks chunks of a sequence on: of the cache's capacity, or of
+// the ring kernel's workgroups (m->attn_defer: -1 that rule, 0 never, 1
+// always). Measured: the 14B tree (9 chunks of 2 spans) 8.62 -> 8.30 ms per
+// step; where the last-arrival merge is short (the chain's 5 one-span chunks, 2
+// or 3 chunks at batch 16 and the 66B tree) the extra launch does not pay.
 constexpr int kAttnDeferChunks = 6;
-bool attn_defer(const msd_model* m, int max_chunks, int nb) {
-  const int chunks = (max_chunks + nb - 1) / nb;
-  if (chunks <= 1 || m->attn_defer == 0) return false;
+bool attn_defer(const msd_model* m, int max_chunks, int batch, const AttnShape& s) {
+  const int chunks = s.ring ? std::min(s.wgs / batch, max_chunks) : (max_chunks + s.nb - 1) / s.nb;
+  if (chunks <= 1 || m->attn_defer == 0) return m->attn_defer == 1 && s.ring && max_chunks > 1;
   return m->attn_defer == 1 || chunks >= kAttnDeferChunks;
 }
 
@@ -1008,9 +1021,11 @@ msd_status verify_launch(const msd_model* m, msd_kv_cache* kv, const msd_block* 
     aa.q_per_wg = ash.q_per_wg;
     aa.nb = ash.nb;
     aa.ring = ash.ring ? 1 : 0;
+    aa.wgs = ash.wgs;
+    aa.chunk_blocks = ash.chunk_blocks;
     aa.scale = 1.0f / std::sqrt((float)c.head_dim);
     aa.topo = topo;
-    aa.defer = attn_defer(m, L.max_chunks, ash.nb) ? 1 : 0;
+    aa.defer = attn_defer(m, L.max_chunks, blk->batch, ash) ? 1 : 0;
     MSD_HIP(prof_mark(m, MSD_K_ATTN, l, true, stream));
     MSD_HIP(launch_attention(c.head_dim, aa, stream));
     if (aa.defer) MSD_HIP(launch_attention_merge(c.head_dim, aa, stream));
