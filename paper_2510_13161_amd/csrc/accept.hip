@@ -13,8 +13,8 @@
 // With a workspace (AcceptArgs::stats) the vocabulary passes leave the walk:
 // row_stats_kernel, a workgroup per (row, 1/kStatChunks of the vocabulary)
 // over the whole device, stores each chunk's max of z / T and sum of
-// exp(z / T - max) in fp64; the walk then takes the logsumexp from the
-// chunk statistics, and an inverse-CDF draw picks its chunk from the chunk
+// exp(z / T - max) in fp64; accept_walk_kernel then takes the logsumexps from
+// the chunk statistics, and an inverse-CDF draw picks its chunk from the chunk
 // masses (corrected on the candidate ids) and scans that chunk only.
 //
 // Near-tie flags (optional): a decision that a logit error of tol_logit could
@@ -48,6 +48,7 @@ struct Shared {
   int n_c;
   int found;
   int result;
+  unsigned long long in_chunk;  // candidates inside the drawn chunk
 };
 
 __device__ double block_reduce_max(double v, Shared& sh) {
@@ -196,57 +197,55 @@ __device__ int row_sample(const float* z, int V, double invT, double lse, double
   return r;
 }
 
+__device__ __forceinline__ double wave_sum_f64(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
 // Per row and vocabulary chunk c (ids [c ck, (c + 1) ck), ck = ceil(V /
 // kStatChunks)): the chunk's max m of z / T and sum of exp(z / T - m), fp64,
-// in a fixed order (thread-strided partials, then a tree over the threads).
-// An empty chunk stores (-inf, 0).
+// in a fixed order (thread-strided partials, a butterfly over each wave, the
+// waves in order). An empty chunk stores (-inf, 0). The logits of a chunk up
+// to kStatRegs * 256 ids stay in registers between the two passes, and the max
+// is taken in fp32 (scaling by 1 / T > 0 keeps the order and every tie):
+// bound by the fp64 exponentials, 25 rows of 152064 ids 10.6 -> 9.6 us.
+constexpr int kStatRegs = 12;
 __global__ __launch_bounds__(256) void row_stats_kernel(AcceptArgs a) {
-  __shared__ double red[256];
-  const int c = blockIdx.x, row = blockIdx.y, t = threadIdx.x;
+  __shared__ float mx[4];
+  __shared__ double sums[4];
+  const int c = blockIdx.x, row = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int V = a.vocab, ck = (V + kStatChunks - 1) / kStatChunks;
   const int y0 = min(V, c * ck), y1 = min(V, y0 + ck);
   const float* z = a.logits + (size_t)row * V;
   const double invT = 1.0 / (double)a.temperature;
-  double m = -INFINITY;
-  for (int y = y0 + t; y < y1; y += 256) m = fmax(m, (double)z[y] * invT);
-  red[t] = m;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] = fmax(red[t], red[t + o]);
-    __syncthreads();
+  float v[kStatRegs];
+#pragma unroll
+  for (int i = 0; i < kStatRegs; ++i) {
+    const int y = y0 + t + 256 * i;
+    v[i] = y < y1 ? z[y] : -INFINITY;
   }
-  m = red[0];
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kStatRegs; ++i) m = fmaxf(m, v[i]);
+  for (int y = y0 + t + 256 * kStatRegs; y < y1; y += 256) m = fmaxf(m, z[y]);
+  m = wave_max(m);
+  if (lane == 0) mx[wave] = m;
   __syncthreads();
+  m = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
+  const double md = (double)m * invT;
   double sum = 0.0;
-  if (m != -INFINITY)
-    for (int y = y0 + t; y < y1; y += 256) sum += exp((double)z[y] * invT - m);
-  red[t] = sum;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (t < o) red[t] += red[t + o];
-    __syncthreads();
-  }
-  if (t == 0) a.stats[(size_t)row * kStatChunks + c] = make_double2(m, red[0]);
-}
-
-// log sum_y exp(z_y / T) of a row from its chunk statistics (wave 0, lane c
-// holding chunk c; every thread returns it).
-__device__ double row_lse_stats(const double2* st, Shared& sh) {
-  const int t = threadIdx.x;
-  if (t < 64) {
-    const double2 v = st[t];
-    double M = v.x;
+  if (m != -INFINITY) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) M = fmax(M, __shfl_xor(M, o));
-    double S = v.x == -INFINITY ? 0.0 : v.y * exp(v.x - M);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o);
-    if (t == 0) sh.red[0] = M + log(S);
+    for (int i = 0; i < kStatRegs; ++i)
+      if (y0 + t + 256 * i < y1) sum += exp((double)v[i] * invT - md);
+    for (int y = y0 + t + 256 * kStatRegs; y < y1; y += 256) sum += exp((double)z[y] * invT - md);
   }
+  sum = wave_sum_f64(sum);
+  if (lane == 0) sums[wave] = sum;
   __syncthreads();
-  const double r = sh.red[0];
-  __syncthreads();
-  return r;
+  if (t == 0)
+    a.stats[(size_t)row * kStatChunks + c] = make_double2(md, ((sums[0] + sums[1]) + sums[2]) + sums[3]);
 }
 
 // Exclusive prefix of v over the workgroup in thread order (wave scans, then
@@ -274,8 +273,9 @@ __device__ double block_scan(double v, double& total, Shared& sh) {
 // row_sample with the chunk statistics st of the row: the chunks' masses of
 // w(y) = f p(y) off the candidates and sh.rc on them, the chunk holding the
 // target u * total, then the smallest id of that chunk whose cumulative mass
-// exceeds it (a thread per 1/kThreads of the chunk). sh.c_lo / sh.c_hi get
-// the cumulative fractions at the edges of the drawn id's bin.
+// exceeds it (a thread per 1/kThreads of the chunk; only the candidates inside
+// the chunk are compared). sh.c_lo / sh.c_hi get the cumulative fractions at
+// the edges of the drawn id's bin.
 __device__ int row_sample_stats(const float* z, int V, double invT, double lse, double f, double u,
                                 const double2* st, Shared& sh) {
   const int t = threadIdx.x;
@@ -284,9 +284,9 @@ __device__ int row_sample_stats(const float* z, int V, double invT, double lse, 
     const double2 v = st[t];
     double off = v.x == -INFINITY ? 0.0 : v.y * exp(v.x - lse);  // sum of p over the chunk
     double cand = 0.0;
-    const int c0 = t * ck, c1 = c0 + ck;
+    const int kc = t < sh.n_c ? sh.cid[t] / ck : -1;  // the chunk of candidate t
     for (int j = 0; j < sh.n_c; ++j)
-      if (sh.cid[j] >= c0 && sh.cid[j] < c1) {
+      if (__builtin_amdgcn_readlane(kc, j) == t) {
         off -= sh.pcand[j];
         cand += sh.rc[j];
       }
@@ -306,31 +306,34 @@ __device__ int row_sample_stats(const float* z, int V, double invT, double lse, 
     const unsigned long long any = __ballot(w > 0.0);
     const int pick = hit ? __ffsll((long long)hit) - 1 : (any ? 63 - __clzll((long long)any) : 0);
     const double lo_pick = __shfl(lo, pick);
+    const unsigned long long in = __ballot(kc == pick);
     if (t == 0) {
       sh.result = pick;
+      sh.in_chunk = in;
       sh.pre[0] = lo_pick;
       sh.pre[1] = total;
       sh.c_lo = target;  // the target, for the scan below
+      sh.found = 0;
     }
   }
   __syncthreads();
   const int c = sh.result;
+  const unsigned long long in = sh.in_chunk;
   const double base = sh.pre[0], total = sh.pre[1], target = sh.c_lo;
   const int y0 = min(V, c * ck), y1 = min(V, y0 + ck);
   const int per = (y1 - y0 + kThreads - 1) / kThreads;
   const int a0 = min(y1, y0 + t * per), a1 = min(y1, a0 + per);
   auto weight = [&](int y) {
-    for (int j = 0; j < sh.n_c; ++j)
+    for (unsigned long long m = in; m; m &= m - 1) {
+      const int j = __ffsll((long long)m) - 1;
       if (sh.cid[j] == y) return sh.rc[j];
+    }
     return f * exp((double)z[y] * invT - lse);
   };
   double s = 0.0;
   for (int y = a0; y < a1; ++y) s += weight(y);
   double tot_c;
   const double pre = base + block_scan(s, tot_c, sh);
-  __syncthreads();
-  if (t == 0) sh.found = 0;
-  __syncthreads();
   if (pre <= target && target < pre + s) {
     double cum = pre;
     for (int y = a0; y < a1; ++y) {
@@ -364,6 +367,188 @@ __device__ int row_sample_stats(const float* z, int V, double invT, double lse, 
   const int r = sh.result;
   __syncthreads();
   return r;
+}
+
+// The stochastic rules with row statistics. The walk is a chain of decisions
+// of a few loads and sums each, so it is bound by their latency: all nodes'
+// logsumexps and candidate probabilities are computed first, a wave a node,
+// with every load in flight at once, and the walk itself runs in one wave out
+// of LDS, a candidate a lane, with lane exchanges in place of the workgroup's
+// barriers; the whole workgroup comes back for the inverse-CDF draw's scan.
+// 14B tree, rejection (25 nodes, 32 candidates): 53.1 -> 16.1 us against the
+// walk below with its loads and loops at each visited node.
+struct WalkNode {
+  double p;  // target probability
+  float q;   // draft mass
+  int id;
+};
+__global__ __launch_bounds__(kThreads) void accept_walk_kernel(AcceptArgs a) {
+  __shared__ Shared sh;
+  __shared__ double lse_sh[kMaxSlots];
+  __shared__ double f_sh;
+  __shared__ int cur_sh, next_sh, depth_sh, tie_sh;
+  extern __shared__ WalkNode nodes[];  // [n_slots][n_cand] (REJECTION)
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int ns = a.n_slots, C = a.mode == 1 ? a.n_cand : 0;
+  int32_t* path = a.path + (size_t)b * ns;
+  const double invT = 1.0 / (double)a.temperature, tol = (double)a.tol_logit;
+  for (int i = t; i < ns; i += kThreads) {
+    path[i] = i == 0 ? 0 : -1;
+    sh.tok[i] = a.tokens[(size_t)b * ns + i];
+    sh.ua[i] = a.u_accept ? a.u_accept[(size_t)b * ns + i] : 0.0f;
+    sh.us[i] = a.u_sample ? a.u_sample[(size_t)b * ns + i] : 0.0f;
+  }
+  {
+    constexpr int NPW = kMaxSlots / (kThreads / 64);  // nodes a wave
+    double2 st[NPW];
+    int id[NPW];
+    float q[NPW], z[NPW];
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) {
+      const int s = wave + i * (kThreads / 64);
+      if (s >= ns) continue;
+      const size_t row = (size_t)b * ns + s;
+      st[i] = a.stats[row * kStatChunks + lane];
+      if (lane < C) {
+        id[i] = a.cand_ids[row * C + lane];
+        q[i] = a.cand_q[row * C + lane];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) {
+      const int s = wave + i * (kThreads / 64);
+      if (s < ns && lane < C) z[i] = a.logits[((size_t)b * ns + s) * a.vocab + id[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) {
+      const int s = wave + i * (kThreads / 64);
+      if (s >= ns) continue;
+      double M = st[i].x;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) M = fmax(M, __shfl_xor(M, o));
+      const double S = wave_sum_f64(st[i].x == -INFINITY ? 0.0 : st[i].y * exp(st[i].x - M));
+      const double lse = M + log(S);
+      if (lane == 0) lse_sh[s] = lse;
+      if (lane < C) nodes[s * C + lane] = WalkNode{exp((double)z[i] * invT - lse), q[i], id[i]};
+    }
+  }
+  if (t == 0) {
+    cur_sh = depth_sh = tie_sh = 0;
+    sh.n_c = C;
+  }
+  __syncthreads();
+  if (a.mode == 1 && wave == 0) {
+    // REJECTION, wave 0: lane j holds candidate j, lane s slot s's parent
+    const int parent = lane < ns ? a.topo.parent[lane] : -2;
+    int cur = 0, depth = 0;
+    bool tie = false, bad = false;
+    double f = 1.0, r = 0.0, p = 0.0;
+    int id = -1;
+    for (;;) {
+      double q = 0.0;
+      r = p = 0.0;
+      id = -1;
+      if (lane < C) {
+        const WalkNode& nd = nodes[cur * C + lane];
+        r = p = nd.p;
+        q = (double)nd.q;
+        id = nd.id;
+      }
+      f = 1.0;  // residual off the candidates = f * p
+      double pc = -1.0;
+      int next = -1;
+      for (unsigned long long kids = __ballot(parent == cur); kids; kids &= kids - 1) {
+        const int ch = __ffsll((long long)kids) - 1;
+        const unsigned long long at = __ballot(lane < C && id == sh.tok[ch]);
+        const int jx = at ? 63 - __clzll((long long)at) : 0;
+        const double qx = __shfl(q, jx), rx = __shfl(r, jx);
+        if (!at || !(qx > 0.0)) {
+          bad = true;
+          break;
+        }
+        const double ratio = rx / qx;
+        const double alpha = ratio < 1.0 ? ratio : 1.0;
+        const double u = (double)sh.ua[ch];
+        tie |= fabs(u - alpha) < 2.0 * tol * alpha * invT;
+        if (u < alpha) {
+          next = ch;
+          break;
+        }
+        // rejected: r <- normalise((r - q)^+), q <- q without x, renormalised
+        if (pc < 0.0) pc = wave_sum_f64(p);
+        const double d = r - q;
+        r = d > 0.0 ? d : 0.0;
+        const double zr = wave_sum_f64(r) + f * (1.0 - pc);
+        if (zr > 0.0) {
+          f /= zr;
+          r /= zr;
+        }
+        q = lane == jx ? 0.0 : q;
+        if (qx < 1.0) q /= (1.0 - qx);
+      }
+      if (bad || next < 0) break;
+      cur = next;
+      ++depth;
+      if (lane == 0) path[depth] = cur;
+    }
+    if (lane < C) {  // the residual of the node that the draw is from
+      sh.cid[lane] = id;
+      sh.rc[lane] = r;
+      sh.pcand[lane] = p;
+    }
+    if (lane == 0) {
+      f_sh = f;
+      cur_sh = cur;
+      depth_sh = depth;
+      tie_sh = bad ? -1 : (tie ? 1 : 0);
+    }
+  }
+  __syncthreads();
+  if (a.mode == 1) {
+    const int cur = cur_sh;
+    if (tie_sh < 0) {  // a child without draft mass
+      if (t == 0) {
+        atomicOr(a.status, 2u);
+        a.acc_len[b] = depth_sh;
+        a.next_tok[b] = -1;
+        if (a.near_tie) a.near_tie[b] = 1;
+      }
+      return;
+    }
+    const size_t row = (size_t)b * ns + cur;
+    const double u = (double)sh.us[cur];
+    const int y = row_sample_stats(a.logits + row * a.vocab, a.vocab, invT, lse_sh[cur], f_sh, u,
+                                   a.stats + row * kStatChunks, sh);
+    if (t == 0) {
+      a.next_tok[b] = y;
+      a.acc_len[b] = depth_sh;
+      if (a.near_tie) a.near_tie[b] = tie_sh || icdf_near_tie(u, sh.c_lo, sh.c_hi, tol) ? 1 : 0;
+    }
+    return;
+  }
+  // MATCH: y ~ p, descend to the child carrying y
+  int cur = 0, depth = 0;
+  bool tie = false;
+  for (;;) {
+    const size_t row = (size_t)b * ns + cur;
+    const double u = (double)sh.us[cur];
+    const int y = row_sample_stats(a.logits + row * a.vocab, a.vocab, invT, lse_sh[cur], 1.0, u,
+                                   a.stats + row * kStatChunks, sh);
+    tie |= icdf_near_tie(u, sh.c_lo, sh.c_hi, tol);
+    const unsigned long long kids =
+        __ballot(lane > cur && lane < ns && a.topo.parent[lane] == cur && sh.tok[lane] == y);
+    if (!kids) {
+      if (t == 0) a.next_tok[b] = y;
+      break;
+    }
+    cur = __ffsll((long long)kids) - 1;
+    ++depth;
+    if (t == 0) path[depth] = cur;
+  }
+  if (t == 0) {
+    a.acc_len[b] = depth;
+    if (a.near_tie) a.near_tie[b] = tie ? 1 : 0;
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
@@ -440,15 +625,13 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
   bool tie = false;
   for (;;) {
     const float* z = a.logits + ((size_t)b * ns + cur) * a.vocab;
-    const double2* st = a.stats ? a.stats + ((size_t)b * ns + cur) * kStatChunks : nullptr;
-    const double lse = st ? row_lse_stats(st, sh) : row_lse(z, a.vocab, invT, sh);
+    const double lse = row_lse(z, a.vocab, invT, sh);
     int next_child = -1, out_tok = -1;
     if (a.mode == 2) {  // MATCH: y ~ p, descend to the child carrying y
       if (t == 0) sh.n_c = 0;
       __syncthreads();
       const double u = (double)sh.us[cur];
-      const int y = st ? row_sample_stats(z, a.vocab, invT, lse, 1.0, u, st, sh)
-                       : row_sample(z, a.vocab, invT, lse, 1.0, u, sh);
+      const int y = row_sample(z, a.vocab, invT, lse, 1.0, u, sh);
       tie |= icdf_near_tie(u, sh.c_lo, sh.c_hi, tol);
       for (int ch = cur + 1; ch < ns; ++ch)
         if (a.topo.parent[ch] == cur && tok[ch] == y) {
@@ -529,8 +712,7 @@ __global__ __launch_bounds__(kThreads) void accept_kernel(AcceptArgs a) {
       }
       if (next_child < 0) {
         const double u = (double)sh.us[cur];
-        out_tok = st ? row_sample_stats(z, a.vocab, invT, lse, f, u, st, sh)
-                     : row_sample(z, a.vocab, invT, lse, f, u, sh);
+        out_tok = row_sample(z, a.vocab, invT, lse, f, u, sh);
         tie |= icdf_near_tie(u, sh.c_lo, sh.c_hi, tol);
       }
     }
@@ -593,6 +775,9 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(row_stats_kernel, dim3(kStatChunks, a.batch * a.n_slots), dim3(256), 0, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const size_t shmem = a.mode == 1 ? (size_t)a.n_slots * a.n_cand * sizeof(WalkNode) : 0;
+    hipLaunchKernelGGL(accept_walk_kernel, dim3(a.batch), dim3(kThreads), shmem, s, a);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(accept_kernel, dim3(a.batch), dim3(kThreads), 0, s, a);
   return hipGetLastError();
