@@ -417,7 +417,10 @@ __global__ __launch_bounds__(kThreads) void accept_walk_kernel(AcceptArgs a) {
 #pragma unroll
     for (int i = 0; i < NPW; ++i) {
       const int s = wave + i * (kThreads / 64);
-      if (s < ns && lane < C) z[i] = a.logits[((size_t)b * ns + s) * a.vocab + id[i]];
+      // candidates count at the nodes that the walk reaches only: at the others
+      // (and past the vocabulary) an id may be anything and is not looked up
+      if (s < ns && lane < C)
+        z[i] = (unsigned)id[i] < (unsigned)a.vocab ? a.logits[((size_t)b * ns + s) * a.vocab + id[i]] : -INFINITY;
     }
 #pragma unroll
     for (int i = 0; i < NPW; ++i) {

@@ -380,6 +380,41 @@ def test_stochastic_seeded_workload_inputs(vmodel, mode, ws):
                              si.u_accept, si.u_sample, ws=ws), want)
 
 
+@pytest.mark.parametrize("mode,n,n_cand", [("rejection", 64, 64), ("rejection", 64, 1), ("rejection", 17, 33),
+                                           ("rejection", 1, 5), ("match", 64, 1), ("match", 16, 1)])
+def test_stochastic_walk_with_statistics_at_its_edges(vmodel, mode, n, n_cand):
+    """The walk that first computes every node's logsumexp and candidate
+    probabilities (a wave a node, 16 waves) at the largest block and candidate
+    count, at one candidate, at one slot and at node counts around its wave
+    count. A node that the walk does not reach may hold any candidate ids
+    (here ids outside the vocabulary): they are not looked up."""
+    model, V = vmodel
+    g = np.random.default_rng(800 + V + n + n_cand + (mode == "match"))
+    B = 4
+    # every slot has at most one child with one candidate, else up to 3
+    parent = np.full(n, -1)
+    for s in range(1, n):
+        parent[s] = s - 1 if n_cand < 3 or mode == "match" else max(0, s - 1 - int(g.integers(0, 3)))
+    kids = _children(parent)
+    plan = []
+    for b in range(B):
+        path, want = [0], (0, 1, n // 2, n)[b]
+        while len(path) <= want and kids[path[-1]]:
+            path.append(kids[path[-1]][0])  # the first child: siblings are not tried
+        plan.append((path, int(g.integers(0, V))))
+    tok, z, cand, q, ua, us = _stochastic_case(g, parent, B, V, plan, mode, 1.0, n_cand=max(n_cand, 4))
+    if n_cand < 4:  # the draft's token alone, with all of its mass
+        cand, q = cand[..., :1].copy(), np.ones((B, n, 1), np.float32)
+    want = _oracle_accept(parent, tok, z, mode, 1.0, cand, q, ua, us)
+    assert all(want[b][0] == len(plan[b][0]) - 1 for b in range(B)) and (n == 1 or want[3][0] > 0)
+    for b in range(B):
+        reached = set(int(v) for v in want[b][2])
+        for s in range(n):
+            if s not in reached:
+                cand[b, s] = g.choice([-1, -(1 << 31), V, (1 << 31) - 1], size=cand.shape[-1])
+    _assert_same(_run_accept(model, parent, tok, z, mode, 1.0, cand, q, ua, us, ws=True), want)
+
+
 def test_rejection_child_outside_candidates_sets_status(vmodel):
     """A REJECTION child whose token has no draft mass at its parent is a
     device-detected error (the oracle refuses it too)."""
