@@ -157,7 +157,8 @@ typedef struct msd_model msd_model;
  * tiles may run the kernel that shares the activation through LDS: 3 unset;
  * at 3 it runs where its workgroups balance the compute units),
  * MSD_ROWS_MIN_TILES (forces that kernel on GEMMs with at least this many
- * tiles), MSD_ROWS_MAX_SPLITS (its splits of K at most, 4 unset) and
+ * tiles), MSD_ROWS_MAX_SPLITS (its splits of K at most, 4 unset; the last
+ * dispatch round of a GEMM of several rounds has its own) and
  * MSD_ROWS_NARROW (narrower GEMMs of 3 or more row tiles in that kernel
  * with many splits and their split sum and epilogue in a second kernel: 0
  * never, 2 at any size; unset, for matrices of 32M weights or more at 3 row

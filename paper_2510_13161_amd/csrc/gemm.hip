@@ -929,7 +929,8 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
 // tile, and the compute waves keep only weights in flight (D k-steps). One
 // barrier per k-step passes the slots between the loader and the compute
 // waves. With splits of K each split writes its partial of the tile and
-// gemm_epi_kernel sums them and runs the epilogues.
+// gemm_epi_kernel sums them and runs the epilogues; tiles before a.split_from
+// run whole K and their epilogues here.
 template <int MT>
 __host__ __device__ constexpr int rows_depth() {  // weight k-steps in flight per compute wave
   return MT >= 8 ? 3 : (MT == 7 ? 4 : (MT >= 4 ? 6 : 4));
@@ -962,9 +963,12 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tw = blockIdx.x / a.splits, s = blockIdx.x - tw * a.splits;
+  // the workgroups before `whole` run whole K
+  const int whole = a.split_from / NW, x = (int)blockIdx.x - whole;
+  const int splits = x < 0 ? 1 : a.splits;
+  const int tw = x < 0 ? (int)blockIdx.x : whole + x / splits, s = x < 0 ? 0 : x % splits;
   const int KS = a.K >> 5;
-  const int kb = (int)((int64_t)KS * s / a.splits), ke = (int)((int64_t)KS * (s + 1) / a.splits);
+  const int kb = (int)((int64_t)KS * s / splits), ke = (int)((int64_t)KS * (s + 1) / splits);
   const int n = ke - kb;
   // k-steps from a point rotated by the workgroup's tiles (fixed per tile:
   // sums stay bit-reproducible), so that concurrent workgroups read different
@@ -1003,11 +1007,11 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
       }
     }
     // with splits of K the epilogue kernel takes the rows' norms from memory:
-    // the loaders of the first MT workgroups merge them, a row tile each, while
-    // their compute waves store the partials
+    // the loaders of the first MT split workgroups merge them, a row tile each,
+    // while their compute waves store the partials
     if constexpr (has_norm<EPI>()) {
-      if (a.splits > 1 && a.norm_rows) {
-        for (int mt = blockIdx.x; mt < MT; mt += gridDim.x) {
+      if (splits > 1 && a.norm_rows) {
+        for (int mt = x; mt < MT; mt += (int)gridDim.x - whole) {
           float mu, rs;
           row_norm(a, mt, mu, rs);
           if (lane < 16 && 16 * mt + lane < a.M) a.norm_rows[16 * mt + lane] = make_float2(mu, rs);
@@ -1021,7 +1025,7 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
   // k-loop (the summaries' registers are free then) and left in LDS for the
   // epilogues; barrier 0 below orders the writes before any read
   if constexpr (has_norm<EPI>()) {
-    for (int mt = wave; mt < MT && a.splits == 1; mt += NW) {
+    for (int mt = wave; mt < MT && splits == 1; mt += NW) {
       float mu, rs;
       row_norm(a, mt, mu, rs);
       if (lane < 16) norm_sh[16 * mt + lane] = make_float2(mu, rs);
@@ -1116,10 +1120,10 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
   }
   if (t >= a.n_tiles) return;
 
-  if (a.splits > 1) {
+  if (splits > 1) {
     // this split's partial of the tile (all row tiles); gemm_epi_kernel sums
     // the splits in split order and runs the epilogue
-    float* part = a.partial + ((size_t)t * a.splits + s) * TF + lane * 4;
+    float* part = a.partial + ((size_t)(t - a.split_from) * splits + s) * TF + lane * 4;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -1139,8 +1143,9 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
 // Bound by its chain of loads and by instruction issue, not by bytes: at 144
 // rows one wave a unit that merged the row norms itself and took its splits
 // 4 at a time in series was 15.3 us for the 14B gate+up, 13.6 for QKV, 10.3
-// for O and down (8.4 at 36 rows); the sum over 4 waves takes O and down to 9.8 (5.5), the norms from memory
-// the gate+up pair (both kernels) from 104 to 96-101, QKV's from 42.3 to 37.4.
+// for O and down (8.4 at 36 rows); the sum over 4 waves takes O and down to
+// 9.8 (5.5), the norms from memory the gate+up pair (both kernels) from 104 to
+// 96-101, QKV's from 42.3 to 37.4.
 template <int EPI, int SW>
 __global__ __launch_bounds__(256, EPI == EPI_RESID ? 3 : 4) void gemm_epi_kernel(GemmArgs a) {
   constexpr int JT = 4;
@@ -1150,10 +1155,10 @@ __global__ __launch_bounds__(256, EPI == EPI_RESID ? 3 : 4) void gemm_epi_kernel
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int u = SW == 1 ? blockIdx.x * 4 + wave : blockIdx.x, w = SW == 1 ? 0 : wave;
-  const int t = u / a.MT, mt = u - t * a.MT;
+  const int ts = u / a.MT, mt = u - ts * a.MT, t = a.split_from + ts;
   if (t >= a.n_tiles) return;
   const uint32_t TF = (uint32_t)a.MT * JT * 256;
-  const float* part = a.partial + (size_t)t * a.splits * TF + mt * JT * 256 + lane * 4;
+  const float* part = a.partial + (size_t)ts * a.splits * TF + mt * JT * 256 + lane * 4;
   EpiIn in;
   if constexpr (EPI == EPI_QKV) in.L = row_len(a, 16 * mt + (lane & 15));
   float2 norm = make_float2(0.0f, 1.0f);
@@ -1197,7 +1202,7 @@ __global__ __launch_bounds__(256, EPI == EPI_RESID ? 3 : 4) void gemm_epi_kernel
 // 4 waves a (tile, row tile) from 4 splits on, 1 below
 template <int EPI>
 hipError_t launch_epi_kernel(const GemmArgs& a, hipStream_t s, hipEvent_t stop) {
-  const unsigned units = (unsigned)(a.n_tiles * a.MT);
+  const unsigned units = (unsigned)((a.n_tiles - a.split_from) * a.MT);
   if (a.splits >= 4)
     hipExtLaunchKernelGGL((gemm_epi_kernel<EPI, 4>), dim3(units), dim3(256), 0, s, nullptr, stop, 0, a);
   else
@@ -1207,9 +1212,10 @@ hipError_t launch_epi_kernel(const GemmArgs& a, hipStream_t s, hipEvent_t stop) 
 
 template <int MT, int NW, int EPI>
 hipError_t launch_rows(const GemmArgs& a, hipStream_t s, LaunchEvents ev) {
-  const int wgs = (a.n_tiles + NW - 1) / NW;
+  const int wgs = (a.n_tiles + NW - 1) / NW, whole = a.split_from / NW;
   const bool two = a.splits > 1;
-  hipExtLaunchKernelGGL((gemm_rows_kernel<MT, NW, EPI>), dim3(wgs * a.splits), dim3(64 * (NW + 1)), 0, s,
+  if (a.split_from % NW != 0 || whole >= wgs || (whole > 0 && !two)) return hipErrorInvalidValue;
+  hipExtLaunchKernelGGL((gemm_rows_kernel<MT, NW, EPI>), dim3(whole + (wgs - whole) * a.splits), dim3(64 * (NW + 1)), 0, s,
                         ev.start, two ? nullptr : ev.stop, 0, a);
   if (two) {
     const hipError_t e = hipGetLastError();

@@ -63,6 +63,8 @@ struct GemmArgs {
                            // activation through LDS; then waves = 4, and with
                            // splits > 1 a second kernel sums the splits and runs
                            // the epilogue)
+  int32_t split_from;      // wg_tiles > 1 and splits > 1: the first 64-column tile whose
+                           // K is split (a multiple of wg_tiles); those before run whole K
   int32_t row_groups;      // > 0: the row tiles in that many groups of at most 3, a
                            // workgroup each (64-column tiles of 8 waves, splits = 1)
   int32_t map;

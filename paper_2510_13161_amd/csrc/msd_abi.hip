@@ -41,8 +41,8 @@ struct msd_model {
   int32_t rows_min_tiles = 256;    // 64-column tiles of a GEMM that takes the LDS-shared kernel
   int32_t rows_min_mt = 3;         // row tiles from which it does
   bool rows_forced = false;        // MSD_ROWS_MIN_TILES set: no balance check
-  int32_t rows_narrow = 1;         // narrow GEMMs from 5 row tiles on: many splits, deferred epilogue
-                                   // (0 off, 1 large matrices, 2 any)
+  int32_t rows_narrow = 1;         // narrow GEMMs: many splits, deferred epilogue, or row groups
+                                   // (0 off, 1 by weights, 2 many splits at any size)
   int32_t rows_narrow_mt = 3;      // row tiles from which it does
   int32_t attn_spans = 0;          // attention spans per chunk (0: chosen per call; 1: one-span kernel)
   int32_t attn_defer = -1;         // chunk merge in its own kernel: -1 by chunk count, 0 never, 1 always
@@ -189,11 +189,25 @@ struct GemmShape {
   int n_tiles, K, splits, waves, jt;
   int wg_tiles = 1;
   int row_groups = 0;
+  int split_from = 0;
 };
 
 struct Shapes {
   GemmShape qkv, o, up, down, head;
 };
+
+// Wide GEMMs of more workgroups than one dispatch round takes (the LM head):
+// the rounds that are full run whole K, the workgroups of the last one are
+// split in K so that they fill it too (14B vocabulary: 594 workgroups, 82 in the
+// last round; head with top-4 at 144 rows 540-547 -> 470 us). s: their splits,
+// returned: the first tile of the last round, 0 where there is nothing to gain.
+int rows_tail(const msd_model* m, int n_tiles, int K, int per_cu, int* s) {
+  const int slots = m->n_cus * per_cu, wg = (n_tiles + 3) / 4;
+  const int full = wg / slots * slots, last = wg - full;
+  if (full == 0 || last == 0) return 0;
+  *s = std::min(std::min(slots / last, kRowsNarrowSplits), K / 32 / 8);
+  return *s > 1 ? 4 * full : 0;
+}
 
 // Small matrices at several row tiles (fewer than m->rows_min_tiles 64-column
 // tiles): the row tiles in groups of at most 3, whole K, as many groups as fit
@@ -284,6 +298,9 @@ Shapes shapes(const msd_model* m, int M, bool lean) {
       g->wg_tiles = 4;
       g->waves = 4;
       g->splits = rs;
+      int tail = 0;
+      if (rs == 1 && !lean) g->split_from = rows_tail(m, g->n_tiles, g->K, per_cu, &tail);
+      if (g->split_from > 0) g->splits = tail;
       continue;
     }
     if (mt >= 4) {  // the LDS-shared kernel switched off
@@ -342,7 +359,7 @@ Layout layout_of(const msd_model* m, const Shapes& s, int batch, int n_slots, in
   int max_tiles = 0;
   for (const GemmShape* g : {&s.qkv, &s.o, &s.up, &s.down, &s.head}) {
     if (g->splits > 1) {
-      const size_t p = (size_t)g->n_tiles * g->splits * L.MT * g->jt * 256 * sizeof(float);
+      const size_t p = (size_t)(g->n_tiles - g->split_from) * g->splits * L.MT * g->jt * 256 * sizeof(float);
       part = p > part ? p : part;
       max_tiles = g->n_tiles > max_tiles ? g->n_tiles : max_tiles;
     }
@@ -500,6 +517,7 @@ GemmArgs gemm_base(const msd_model* m, const Layout& L, char* ws, int M, const G
   g.jt = sh.jt;
   g.wg_tiles = sh.wg_tiles;
   g.row_groups = sh.row_groups;
+  g.split_from = sh.split_from;
   g.partial = reinterpret_cast<float*>(ws + L.partial);
   g.counters = reinterpret_cast<int32_t*>(ws + L.counters);
   // the rows' norms between a GEMM and its epilogue kernel ([M], at most the

@@ -754,6 +754,71 @@ def test_rows_narrow_deferred_epilogue(monkeypatch, shape, batch):
     print("narrow deferred", shape, batch, _compare(case, gr, seqs))
 
 
+@pytest.mark.parametrize("path", ["groups", "rows", "narrow"])
+@pytest.mark.parametrize("rows", [16, 17, 33, 49, 64, 65, 81, 97, 113, 128])
+def test_gemm_row_tile_counts(monkeypatch, rows, path):
+    """Every row tile count from 1 to 8 at its first or last row (9 tiles: the
+    batch 16 cases above) on widths whose column tile counts are no multiple of
+    4 or 8: small matrices in groups of row tiles (the default: uneven groups,
+    a column tile past the last), the kernel that shares the activation
+    through LDS forced on every GEMM, and the same with splits of K and the
+    epilogue kernel."""
+    _torch()
+    if path == "rows":
+        monkeypatch.setenv("MSD_ROWS_MIN_MT", "2")
+        monkeypatch.setenv("MSD_ROWS_MIN_TILES", "1")
+    elif path == "narrow":
+        monkeypatch.setenv("MSD_ROWS_NARROW", "2")
+    w = synth.Workload("row_tiles", ROWS_RAGGED, rows, (1, 90), "chain", 0, ee_layer=1, kappa=4, seed=50 + rows)
+    assert w.batch * w.n_slots == rows
+    case = H.GpuCase(w)
+    case.reset_len()
+    gr = case.run(ee=True)
+    weights = synth.host_weights(case.shape, w.seed)
+    # the first and last rows of the first and last row tile, and one between
+    seqs = {b: H.oracle_sequence(case.shape, w, case.si, b, weights=weights)
+            for b in sorted({0, 15, rows // 2, (rows - 1) // 16 * 16, rows - 1})}
+    print("row tiles", path, rows, _compare(case, gr, seqs))
+
+
+@pytest.mark.parametrize("heads,batch,ctx,capacity,defer", [
+    (16, 12, (1, 3000), 8192, 0), (16, 12, (1, 3000), 8192, 1), (8, 100, (1, 700), 4096, 0),
+    (8, 100, (1, 700), 4096, 1), (16, 1, (1800, 1800), 32768, 1), (16, 1, (1, 1), 32768, 0)])
+def test_attention_ring_planned_chunks(monkeypatch, heads, batch, ctx, capacity, defer):
+    """Ring-fed attention with chunks that the device sizes from the lengths
+    (one sequence, or a cache of many spans): uneven contexts in a cache much
+    longer than they are, more sequences than a wave has lanes, one sequence of
+    one cached key, the chunks merged by the last to arrive or by the merge
+    kernel. One of the sequences does not fit the cache: it is flagged, its
+    cache rows stay as they were and the others are not disturbed."""
+    torch = _torch()
+    from paper_2510_13161_amd import msd
+    monkeypatch.setenv("MSD_ATTN_DEFER", str(defer))
+    shape = synth.ModelShape(f"h128x{heads}", 2, 512, heads, 2, 128, 1024, 4096, rope_theta=1.0e4)
+    gamma = 8 if batch <= 12 else 0
+    w = synth.Workload("ring_plan", shape, batch, ctx, "chain", gamma, ee_layer=1, kappa=4, seed=61 + batch)
+    case = H.GpuCase(w, capacity=capacity)
+    weights = synth.host_weights(case.shape, w.seed)
+    lens = case.si.ctx_len
+    at = sorted({0, batch // 3, batch - 1, int(np.argmin(lens)), int(np.argmax(lens)), min(63, batch - 1),
+                 min(64, batch - 1)})
+    seqs = {b: H.oracle_sequence(case.shape, w, case.si, b, weights=weights) for b in at}
+    case.reset_len()
+    print("ring planned", heads, batch, defer, _compare(case, case.run(), seqs))
+    if batch == 1:
+        return
+    bad = next(b for b in range(1, batch) if b not in at)
+    case.si.ctx_len[bad] = capacity - w.n_slots + 1
+    case.reset_len()
+    k_before = case.cache.k[:, bad].clone()
+    gr = case.run(commit=False)
+    assert gr.status & msd.MSD_DEV_CAPACITY
+    assert torch.equal(case.cache.k[:, bad], k_before)
+    n = w.n_slots
+    for b, o in seqs.items():
+        assert np.abs(gr.logits[b * n:(b + 1) * n] - o.logits).max() <= H.TOL_LOGIT
+
+
 @pytest.mark.parametrize("spans", [1, 2])
 def test_attention_deferred_merge(monkeypatch, spans):
     """The attention's chunk merge in a kernel of its own, forced, under both
