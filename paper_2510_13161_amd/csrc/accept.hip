@@ -203,6 +203,12 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
+__device__ __forceinline__ double readlane_f64(double v, int j) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)b, j), hi = __builtin_amdgcn_readlane((int)(b >> 32), j);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Per row and vocabulary chunk c (ids [c ck, (c + 1) ck), ck = ceil(V /
 // kStatChunks)): the chunk's max m of z / T and sum of exp(z / T - m), fp64,
 // in a fixed order (thread-strided partials, a butterfly over each wave, the
@@ -285,11 +291,17 @@ __device__ int row_sample_stats(const float* z, int V, double invT, double lse, 
     double off = v.x == -INFINITY ? 0.0 : v.y * exp(v.x - lse);  // sum of p over the chunk
     double cand = 0.0;
     const int kc = t < sh.n_c ? sh.cid[t] / ck : -1;  // the chunk of candidate t
-    for (int j = 0; j < sh.n_c; ++j)
+    // candidate t's masses in lane t, handed round by readlane: an LDS read of
+    // each in turn would be a chain of n_c LDS latencies
+    const double pj = t < sh.n_c ? sh.pcand[t] : 0.0, rj = t < sh.n_c ? sh.rc[t] : 0.0;
+    const int n_c = sh.n_c;
+    for (int j = 0; j < n_c; ++j) {
+      const double pv = readlane_f64(pj, j), rv = readlane_f64(rj, j);
       if (__builtin_amdgcn_readlane(kc, j) == t) {
-        off -= sh.pcand[j];
-        cand += sh.rc[j];
+        off -= pv;
+        cand += rv;
       }
+    }
     double w = f * (off > 0.0 ? off : 0.0) + cand;
     double x = w;
 #pragma unroll
@@ -323,32 +335,48 @@ __device__ int row_sample_stats(const float* z, int V, double invT, double lse, 
   const int y0 = min(V, c * ck), y1 = min(V, y0 + ck);
   const int per = (y1 - y0 + kThreads - 1) / kThreads;
   const int a0 = min(y1, y0 + t * per), a1 = min(y1, a0 + per);
-  auto weight = [&](int y) {
+  auto weight_of = [&](int y, float zy) {
     for (unsigned long long m = in; m; m &= m - 1) {
       const int j = __ffsll((long long)m) - 1;
       if (sh.cid[j] == y) return sh.rc[j];
     }
-    return f * exp((double)z[y] * invT - lse);
+    return f * exp((double)zy * invT - lse);
   };
+  auto weight = [&](int y) { return weight_of(y, z[y]); };
+  // a thread's first PRE ids are loaded together and their weights kept for the
+  // second pass (all of them up to a vocabulary of 262144)
+  constexpr int PRE = 4;
+  float zv[PRE];
+  double wv[PRE];
+#pragma unroll
+  for (int i = 0; i < PRE; ++i) zv[i] = a0 + i < a1 ? z[a0 + i] : 0.0f;
   double s = 0.0;
-  for (int y = a0; y < a1; ++y) s += weight(y);
+#pragma unroll
+  for (int i = 0; i < PRE; ++i) {
+    wv[i] = a0 + i < a1 ? weight_of(a0 + i, zv[i]) : 0.0;
+    s += wv[i];
+  }
+  for (int y = a0 + PRE; y < a1; ++y) s += weight(y);
   double tot_c;
   const double pre = base + block_scan(s, tot_c, sh);
   if (pre <= target && target < pre + s) {
     double cum = pre;
-    for (int y = a0; y < a1; ++y) {
-      const double w = weight(y);
-      if (w <= 0.0) continue;
+    auto drawn = [&](int y, double w) {  // whether y's bin holds the target
+      if (w <= 0.0) return false;
       const double before = cum;
       cum += w;
-      if (cum > target) {
-        sh.result = y;
-        sh.c_lo = before / total;
-        sh.c_hi = cum / total;
-        sh.found = 1;
-        break;
-      }
-    }
+      if (!(cum > target)) return false;
+      sh.result = y;
+      sh.c_lo = before / total;
+      sh.c_hi = cum / total;
+      sh.found = 1;
+      return true;
+    };
+    bool done = false;
+#pragma unroll
+    for (int i = 0; i < PRE; ++i)
+      if (!done && a0 + i < a1) done = drawn(a0 + i, wv[i]);
+    for (int y = a0 + PRE; y < a1 && !done; ++y) done = drawn(y, weight(y));
   }
   __syncthreads();
   if (!sh.found && t == 0) {
@@ -376,7 +404,8 @@ __device__ int row_sample_stats(const float* z, int V, double invT, double lse, 
 // of LDS, a candidate a lane, with lane exchanges in place of the workgroup's
 // barriers; the whole workgroup comes back for the inverse-CDF draw's scan.
 // 14B tree, rejection (25 nodes, 32 candidates): 53.1 -> 16.1 us against the
-// walk below with its loads and loops at each visited node.
+// walk below with its loads and loops at each visited node, 14.5 with the draw's
+// candidate masses out of registers and its ids loaded together.
 struct WalkNode {
   double p;  // target probability
   float q;   // draft mass
