@@ -119,8 +119,10 @@ int splits_for(const msd_model* m, int n_tiles, int K, int waves, int per_cu) {
 // workgroup sharing the activation through LDS (one workgroup per compute
 // unit from 5 row tiles on, by its LDS ring and registers; two up to 3).
 // Splits of K as for split-K above, for the best balance of
-// ceil(n_tiles / 4) * s workgroups over the units within one dispatch
-// round, at most m->rows_max_splits (each split adds an fp32 partial of the
+// ceil(n_tiles / 4) * s workgroups over the units within two workgroups a unit
+// (one dispatch round, or two from 4 row tiles on: 66B FFN up, 144 workgroup
+// tiles in 3 splits instead of whole K, two layers at 99 rows 1284 -> 1189 us,
+// at 144 1456 -> 1365, at 66 997 -> 945), at most m->rows_max_splits (each split adds an fp32 partial of the
 // whole [M][64] tile to write and read back) and at least 8 k-steps a
 // split. Returns 0 where at 3 row tiles no split count balances at least 3/4
 // of the units (then the split-K kernel runs), unless the kernel is forced;
@@ -132,7 +134,7 @@ int splits_for(const msd_model* m, int n_tiles, int K, int waves, int per_cu) {
 // workgroup a unit then): QKV (108, 2 splits) 118.3 -> 97.2 us, LM head
 // (197) 224.8 -> 166.5 us, its FFN up (144 workgroup tiles: 0.56 at best)
 // 168.8 -> 177.7 us.
-int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu, bool lean) {
+int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu, int lean) {
   const int64_t C = m->n_cus;
   const int64_t wg = (n_tiles + 3) / 4;
   const int max_s = std::max(1, std::min(m->rows_max_splits, (K / 32) / 8));
@@ -140,7 +142,7 @@ int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu, bool lean) {
   double best_bal = 0.0;
   for (int s = 1; s <= max_s; ++s) {
     const int64_t W = wg * s;
-    if (s > 1 && W > per_cu * C) break;
+    if (s > 1 && W > (lean > 0 ? per_cu : 2) * C) break;
     const double bal = (double)W / (double)(C * ((W + C - 1) / C));
     if (bal > best_bal + 1e-9) {
       best = s;
@@ -148,7 +150,7 @@ int rows_splits(const msd_model* m, int n_tiles, int K, int per_cu, bool lean) {
     }
   }
   if (best_bal >= 0.75 || m->rows_forced) return best;
-  return per_cu > 1 ? 0 : (lean ? 1 : best);
+  return per_cu > 1 ? 0 : (lean > 1 ? 1 : best);
 }
 
 // Narrow GEMMs (fewer tiles than m->rows_min_tiles) from 3 row tiles on:
@@ -236,9 +238,10 @@ int row_groups(const msd_model* m, int n_tiles, int mt) {
 // do not fit the compute units (else split-K tiles of 8 waves: 6M weights 10.4
 // -> 8.8 us), at 3 only where the LDS-shared kernel does not balance (14B, 36
 // rows: 63 -> 59 us there).
-// lean: the shapes of the smallest workspace (no split partials where row
-// groups or whole K can stand in), for blocks that then fit the static scratch.
-Shapes shapes(const msd_model* m, int M, bool lean) {
+// lean, for blocks that only then fit the static scratch: 1 without the splits
+// over two dispatch rounds and of a last round, 2 the shapes of the smallest
+// workspace (no split partials where row groups or whole K can stand in).
+Shapes shapes(const msd_model* m, int M, int lean) {
   const msd_model_config& c = m->cfg;
   const int mt = row_tiles(M);
   const bool one = mt == 1;
@@ -270,7 +273,7 @@ Shapes shapes(const msd_model* m, int M, bool lean) {
   // the LM head at one row tile: 128-column tiles of 4 waves, unless its
   // 64-column tiles fit the compute units (split-K tiles of 8 waves as the
   // projections': 4096 x 5120 weights 36.7 -> 16.3 us, 4096 x 1024 14.1 -> 9.5)
-  if (one && (lean || s.head.n_tiles >= m->n_cus)) {
+  if (one && (lean > 1 || s.head.n_tiles >= m->n_cus)) {
     s.head.jt = 8;
     s.head.n_tiles = (c.vocab + 2 * kTileN - 1) / (2 * kTileN);
     s.head.waves = 4;
@@ -280,7 +283,7 @@ Shapes shapes(const msd_model* m, int M, bool lean) {
     const bool wide = g->n_tiles >= m->rows_min_tiles, resid = g == &s.o || g == &s.down;
     const int per_cu = mt <= 3 ? 2 : 1;
     if (!one && !wide && m->rows_narrow == 1 &&
-        (mt >= 4 ? weights <= (lean ? kRowsNarrowMinWeights - 1 : kGroupMaxWeights)
+        (mt >= 4 ? weights <= (lean > 1 ? kRowsNarrowMinWeights - 1 : kGroupMaxWeights)
                  : weights <= kGroupMaxWeightsFewRows && !resid)) {
       g->row_groups = row_groups(m, g->n_tiles, mt);
       g->waves = 8;
@@ -289,7 +292,7 @@ Shapes shapes(const msd_model* m, int M, bool lean) {
     }
     int rs = 0;  // splits of the LDS-shared kernel (4 tiles a workgroup); 0: not taken
     const bool pair_up = g == &s.up && c.act == MSD_ACT_SWIGLU && mt <= 3 && !(one && g->n_tiles <= m->n_cus);
-    if (g->jt == 4 && wide && mt >= m->rows_min_mt && !(lean && pair_up))
+    if (g->jt == 4 && wide && mt >= m->rows_min_mt && !(lean > 1 && pair_up))
       rs = rows_splits(m, g->n_tiles, g->K, per_cu, lean);
     else if (g->jt == 4 && !wide && !pair_up && mt >= m->rows_narrow_mt &&
              (m->rows_narrow == 2 || (m->rows_narrow == 1 && (mt >= 4 || weights >= kRowsNarrowMinWeights))))
@@ -299,7 +302,7 @@ Shapes shapes(const msd_model* m, int M, bool lean) {
       g->waves = 4;
       g->splits = rs;
       int tail = 0;
-      if (rs == 1 && !lean) g->split_from = rows_tail(m, g->n_tiles, g->K, per_cu, &tail);
+      if (rs == 1 && lean == 0) g->split_from = rows_tail(m, g->n_tiles, g->K, per_cu, &tail);
       if (g->split_from > 0) g->splits = tail;
       continue;
     }
@@ -392,14 +395,17 @@ Layout layout_of(const msd_model* m, const Shapes& s, int batch, int n_slots, in
   return L;
 }
 
-// the workspace layout of a block and the GEMM shapes it is for: the lean ones
+// the workspace layout of a block and the GEMM shapes it is for: leaner ones
 // where only they fit the static scratch
 Layout layout(const msd_model* m, int batch, int n_slots, int kappa, int capacity) {
   const int M = batch * n_slots;
-  const Layout L = layout_of(m, shapes(m, M, false), batch, n_slots, kappa, capacity);
+  const Layout L = layout_of(m, shapes(m, M, 0), batch, n_slots, kappa, capacity);
   if (L.total <= kStaticScratchBytes) return L;
-  const Layout lean = layout_of(m, shapes(m, M, true), batch, n_slots, kappa, capacity);
-  return lean.total <= kStaticScratchBytes ? lean : L;
+  for (int lean = 1; lean <= 2; ++lean) {
+    const Layout l = layout_of(m, shapes(m, M, lean), batch, n_slots, kappa, capacity);
+    if (l.total <= kStaticScratchBytes) return l;
+  }
+  return L;
 }
 
 msd_status make_topo(const msd_block* blk, Topo* topo) {

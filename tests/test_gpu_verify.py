@@ -781,6 +781,24 @@ def test_gemm_row_tile_counts(monkeypatch, rows, path):
     print("row tiles", path, rows, _compare(case, gr, seqs))
 
 
+@pytest.mark.parametrize("batch", [7, 16])
+def test_wide_gemm_over_two_dispatch_rounds(batch):
+    """An FFN up projection of 130 workgroup tiles at 63 and 144 rows (4 and 9
+    row tiles): 3 splits of K over two dispatch rounds, the LayerNorm, bias and
+    ReLU in the epilogue kernel, the down projection's K of 1040 k-steps."""
+    _torch()
+    shape = synth.ModelShape("wide_up", 2, 768, 12, 12, 64, 33280, 4096, norm="layer", act="relu", pos="learned",
+                             bias=True, tied_head=True, norm_eps=1.0e-5, max_positions=1024)
+    w = synth.WORKLOADS["14b_batch16"].with_model(shape, batch=batch, ctx=(1, 300), ee_layer=1, kappa=4,
+                                                  seed=71 + batch)
+    case = H.GpuCase(w)
+    case.reset_len()
+    gr = case.run(ee=True)
+    weights = synth.host_weights(case.shape, w.seed)
+    seqs = {b: H.oracle_sequence(case.shape, w, case.si, b, weights=weights) for b in (0, batch // 2, batch - 1)}
+    print("two rounds", batch, _compare(case, gr, seqs))
+
+
 @pytest.mark.parametrize("heads,batch,ctx,capacity,defer", [
     (16, 12, (1, 3000), 8192, 0), (16, 12, (1, 3000), 8192, 1), (8, 100, (1, 700), 4096, 0),
     (8, 100, (1, 700), 4096, 1), (16, 1, (1800, 1800), 32768, 1), (16, 1, (1, 1), 32768, 0)])
