@@ -198,7 +198,8 @@ struct HeadMergeArgs {
   int32_t* argmax; // [M] or null
   float* lse;      // [M] or null
 };
-int head_parts(int n_tiles);  // 256 tiles per part, at most 64 parts
+// 256 tiles per part, at most 64 parts
+inline int head_parts(int n_tiles) { return (n_tiles + 255) / 256; }
 hipError_t launch_head_merge(const HeadMergeArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------------------

@@ -248,8 +248,6 @@ hipError_t launch_rows(const RowsArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int head_parts(int n_tiles) { return (n_tiles + 255) / 256; }
-
 hipError_t launch_head_merge(const HeadMergeArgs& a, hipStream_t s) {
   if (a.kappa < 1 || a.kappa > kMaxKappa) return hipErrorInvalidValue;
   const int parts = head_parts(a.n_tiles);
