@@ -227,13 +227,16 @@ msd_status msd_verify_block(const msd_model* model, msd_kv_cache* kv, const msd_
 /*
  * msd_verify_block without a workspace, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc): the same kernels and outputs, with the scratch in a
- * static device array of the library, MSD_STATIC_SCRATCH_BYTES (64 MiB) per
- * GPU, held from the first msd_model_create on that GPU until the process
- * ends. The call allocates nothing. A block whose workspace
- * (msd_workspace_bytes) exceeds that size returns MSD_ERR_WORKSPACE and
- * enqueues nothing: the 14B-shaped chain and tree blocks and the 66B-shaped
- * tree fit, long-context batches (batch 16 at 8K contexts) do not. Every call
+ * that forbid hipMalloc): the same kernels and outputs, bit for bit, with the
+ * scratch in a static device array of the library: per GPU
+ * MSD_STATIC_SCRATCH_BYTES (64 MiB) and 73 MiB more for the partial sums of
+ * GEMMs split along K, held from the first msd_model_create on that GPU until
+ * the process ends. The call allocates nothing. Every block with
+ * msd_workspace_bytes up to MSD_STATIC_SCRATCH_BYTES fits, and those larger
+ * ones whose workspace exceeds it by split partials only; others return
+ * MSD_ERR_WORKSPACE and enqueue nothing: the 14B-shaped chain and tree blocks
+ * and the 66B-shaped tree fit, long-context batches (batch 16 at 8K contexts)
+ * do not. Every call
  * on one GPU shares its scratch, which keeps the last call's contents (the
  * kernels clear what must start at zero): calls that overlap on one GPU,
  * from different streams or threads, race and must be ordered by the caller.

@@ -564,10 +564,12 @@ msd_status msd_verify_block_static(const msd_model* m, msd_kv_cache* kv, const m
   Layout L;
   msd_status st = verify_prepare(m, kv, blk, ee, argmax, &topo, &L);
   if (st != MSD_OK) return st;
-  if (L.total > kStaticScratchBytes)
-    return fail(MSD_ERR_WORKSPACE, "this block needs " + std::to_string(L.total) +
-                                       " bytes of scratch; the static scratch holds " +
-                                       std::to_string(kStaticScratchBytes) +
+  if (!fits_static(L))
+    return fail(MSD_ERR_WORKSPACE, "this block needs " + std::to_string(L.total - L.split_bytes) +
+                                       " bytes of scratch and " + std::to_string(L.split_bytes) +
+                                       " for split partials; the static scratch holds " +
+                                       std::to_string(MSD_STATIC_SCRATCH_BYTES) + " and " +
+                                       std::to_string(kStaticSplitBytes) +
                                        " (use msd_verify_block with a workspace)");
   if (!m->scratch) return fail(MSD_ERR_HIP, "static scratch address unavailable");
   return verify_launch(m, kv, blk, ee, logits, argmax, lse, static_cast<char*>(m->scratch), topo, L,

@@ -11,8 +11,14 @@
 
 namespace msd {
 
-// Workspace that msd_verify_block_static has.
-constexpr size_t kStaticScratchBytes = MSD_STATIC_SCRATCH_BYTES;
+// Scratch of msd_verify_block_static: MSD_STATIC_SCRATCH_BYTES for a block's
+// workspace without the GEMMs' split partials and counters, and room for
+// those: at most 72 MiB of partials (two workgroups on each of 256 compute
+// units, 4 tiles of 9 row tiles each) and a few KB of counters. With the partials
+// inside the first bound, a block that just fits would have to run other
+// shapes, and so sum in another order, than in a caller's workspace.
+constexpr size_t kStaticSplitBytes = (size_t)73 << 20;
+constexpr size_t kStaticScratchBytes = MSD_STATIC_SCRATCH_BYTES + kStaticSplitBytes;
 
 // What the plan depends on besides the block: the model, its device and the
 // launch-shape overrides.
@@ -91,7 +97,7 @@ inline int splits_for(const PlanInputs* m, int n_tiles, int K, int waves, int pe
 // workgroup a unit then): QKV (108, 2 splits) 118.3 -> 97.2 us, LM head
 // (197) 224.8 -> 166.5 us, its FFN up (144 workgroup tiles: 0.56 at best)
 // 168.8 -> 177.7 us.
-inline int rows_splits(const PlanInputs* m, int n_tiles, int K, int per_cu, int lean) {
+inline int rows_splits(const PlanInputs* m, int n_tiles, int K, int per_cu) {
   const int64_t C = m->n_cus;
   const int64_t wg = (n_tiles + 3) / 4;
   const int max_s = std::max(1, std::min(m->rows_max_splits, (K / 32) / 8));
@@ -99,7 +105,7 @@ inline int rows_splits(const PlanInputs* m, int n_tiles, int K, int per_cu, int 
   double best_bal = 0.0;
   for (int s = 1; s <= max_s; ++s) {
     const int64_t W = wg * s;
-    if (s > 1 && W > (lean > 0 ? per_cu : 2) * C) break;
+    if (s > 1 && W > 2 * C) break;
     const double bal = (double)W / (double)(C * ((W + C - 1) / C));
     if (bal > best_bal + 1e-9) {
       best = s;
@@ -107,7 +113,7 @@ inline int rows_splits(const PlanInputs* m, int n_tiles, int K, int per_cu, int 
     }
   }
   if (best_bal >= 0.75 || m->rows_forced) return best;
-  return per_cu > 1 ? 0 : (lean > 1 ? 1 : best);
+  return per_cu > 1 ? 0 : best;
 }
 
 // Narrow GEMMs (fewer tiles than m->rows_min_tiles) from 3 row tiles on:
@@ -195,12 +201,11 @@ inline int row_groups(const PlanInputs* m, int n_tiles, int mt) {
 // do not fit the compute units (else split-K tiles of 8 waves: 6M weights 10.4
 // -> 8.8 us), at 3 only where the LDS-shared kernel does not balance (14B, 36
 // rows: 63 -> 59 us there).
-// lean, for blocks that only then fit the static scratch: 1 without the splits
-// over two dispatch rounds and of a last round, 2 the shapes of the smallest
-// workspace (no split partials where row groups or whole K can stand in).
-inline Shapes shapes(const PlanInputs* m, int M, int lean) {
+// A function of the row tiles alone: kappa, the cache's capacity and the memory
+// that a caller has change neither the kernels that a block of so many rows runs
+// nor the order of its sums.
+inline Shapes shapes(const PlanInputs* m, int mt) {
   const msd_model_config& c = m->cfg;
-  const int mt = row_tiles(M);
   const bool one = mt == 1;
   Shapes s;
   s.qkv.n_tiles = (c.n_heads + 2 * c.n_kv_heads) * c.head_dim / kTileN;
@@ -230,7 +235,7 @@ inline Shapes shapes(const PlanInputs* m, int M, int lean) {
   // the LM head at one row tile: 128-column tiles of 4 waves, unless its
   // 64-column tiles fit the compute units (split-K tiles of 8 waves as the
   // projections': 4096 x 5120 weights 36.7 -> 16.3 us, 4096 x 1024 14.1 -> 9.5)
-  if (one && (lean > 1 || s.head.n_tiles >= m->n_cus)) {
+  if (one && s.head.n_tiles >= m->n_cus) {
     s.head.jt = 8;
     s.head.n_tiles = (c.vocab + 2 * kTileN - 1) / (2 * kTileN);
     s.head.waves = 4;
@@ -240,7 +245,7 @@ inline Shapes shapes(const PlanInputs* m, int M, int lean) {
     const bool wide = g->n_tiles >= m->rows_min_tiles, resid = g == &s.o || g == &s.down;
     const int per_cu = mt <= 3 ? 2 : 1;
     if (!one && !wide && m->rows_narrow == 1 &&
-        (mt >= 4 ? weights <= (lean > 1 ? kRowsNarrowMinWeights - 1 : kGroupMaxWeights)
+        (mt >= 4 ? weights <= kGroupMaxWeights
                  : weights <= kGroupMaxWeightsFewRows && !resid)) {
       g->row_groups = row_groups(m, g->n_tiles, mt);
       g->waves = 8;
@@ -249,8 +254,8 @@ inline Shapes shapes(const PlanInputs* m, int M, int lean) {
     }
     int rs = 0;  // splits of the LDS-shared kernel (4 tiles a workgroup); 0: not taken
     const bool pair_up = g == &s.up && c.act == MSD_ACT_SWIGLU && mt <= 3 && !(one && g->n_tiles <= m->n_cus);
-    if (g->jt == 4 && wide && mt >= m->rows_min_mt && !(lean > 1 && pair_up))
-      rs = rows_splits(m, g->n_tiles, g->K, per_cu, lean);
+    if (g->jt == 4 && wide && mt >= m->rows_min_mt)
+      rs = rows_splits(m, g->n_tiles, g->K, per_cu);
     else if (g->jt == 4 && !wide && !pair_up && mt >= m->rows_narrow_mt &&
              (m->rows_narrow == 2 || (m->rows_narrow == 1 && (mt >= 4 || weights >= kRowsNarrowMinWeights))))
       rs = rows_narrow_splits(m, g->n_tiles, g->K, per_cu);
@@ -259,7 +264,7 @@ inline Shapes shapes(const PlanInputs* m, int M, int lean) {
       g->waves = 4;
       g->splits = rs;
       int tail = 0;
-      if (rs == 1 && lean == 0) g->split_from = rows_tail(m, g->n_tiles, g->K, per_cu, &tail);
+      if (rs == 1) g->split_from = rows_tail(m, g->n_tiles, g->K, per_cu, &tail);
       if (g->split_from > 0) g->splits = tail;
       continue;
     }
@@ -283,6 +288,7 @@ struct Layout {
   Shapes s;
   size_t x, stats, q, img_x, img_h, img_f, img_attn, img_act, partial, counters, part_o, part_ml,
       tile_ms, tile_top, head_ms, head_top, total;
+  size_t split_bytes;  // of total: split partials past the attention's, and their counters
   int64_t n_counters, n_gemm_counters;
   int32_t MT, max_chunks;
 };
@@ -290,9 +296,10 @@ struct Layout {
 // image bytes of an [M][K] activation
 inline size_t img_bytes(int K, int MT) { return (size_t)(K / 32) * MT * 1024 * sizeof(uint16_t); }
 
-inline Layout layout_of(const PlanInputs* m, const Shapes& s, int batch, int n_slots, int kappa, int capacity) {
+inline Layout layout(const PlanInputs* m, int batch, int n_slots, int kappa, int capacity) {
   const msd_model_config& c = m->cfg;
   const int M = batch * n_slots;
+  const Shapes s = shapes(m, row_tiles(M));
   const int kmax = kappa > 1 ? kappa : 1;
   const int qd = c.n_heads * c.head_dim;
   Layout L{};
@@ -337,12 +344,14 @@ inline Layout layout_of(const PlanInputs* m, const Shapes& s, int batch, int n_s
   // by its own last kernel, the attention's by its own, and every kernel of a
   // step runs after the one before it
   const size_t shared = off;
-  L.partial = take(part);
-  const size_t gemm_end = off;
-  off = shared;
   L.part_o = take(nparts * c.head_dim * sizeof(float));
   L.part_ml = take(nparts * sizeof(float2));
-  off = std::max(off, gemm_end);
+  const size_t attn_end = off;
+  off = shared;
+  L.partial = take(part);
+  off = std::max(off, attn_end);
+  L.split_bytes = off - attn_end + align_up((size_t)L.n_counters * sizeof(int32_t)) -
+                  align_up((size_t)(L.n_counters - L.n_gemm_counters) * sizeof(int32_t));
   L.tile_ms = take((size_t)s.head.n_tiles * M * sizeof(float2));
   L.tile_top = take((size_t)s.head.n_tiles * M * kmax * sizeof(uint64_t));
   const int parts = head_parts(s.head.n_tiles);
@@ -352,17 +361,10 @@ inline Layout layout_of(const PlanInputs* m, const Shapes& s, int batch, int n_s
   return L;
 }
 
-// the workspace layout of a block and the GEMM shapes it is for: leaner ones
-// where only they fit the static scratch
-inline Layout layout(const PlanInputs* m, int batch, int n_slots, int kappa, int capacity) {
-  const int M = batch * n_slots;
-  const Layout L = layout_of(m, shapes(m, M, 0), batch, n_slots, kappa, capacity);
-  if (L.total <= kStaticScratchBytes) return L;
-  for (int lean = 1; lean <= 2; ++lean) {
-    const Layout l = layout_of(m, shapes(m, M, lean), batch, n_slots, kappa, capacity);
-    if (l.total <= kStaticScratchBytes) return l;
-  }
-  return L;
+// Whether the static scratch holds a block: its workspace without the split
+// partials and counters within MSD_STATIC_SCRATCH_BYTES.
+inline bool fits_static(const Layout& L) {
+  return L.total <= kStaticScratchBytes && L.total - L.split_bytes <= MSD_STATIC_SCRATCH_BYTES;
 }
 
 }  // namespace msd

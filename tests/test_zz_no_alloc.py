@@ -103,3 +103,27 @@ def test_static_scratch_rejects_blocks_beyond_its_size():
     torch.cuda.synchronize()
     assert bool((argmax == -7).all()) and int(cache.status.item()) == 0
     model.close()
+
+
+def test_static_scratch_with_split_partials_past_its_size():
+    """A block whose workspace exceeds the static scratch by split partials of
+    the LM head runs there all the same, with the bits of the workspace call;
+    and its logits are the same bits for every early-exit width (kappa sizes
+    buffers only, not the GEMMs' splits)."""
+    import dataclasses
+    _torch()
+    from paper_2510_13161_amd import msd
+    case = H.GpuCase(synth.WORKLOADS["14b_batch16"].with_model(synth.DRAFT06B, ctx=(40, 60), ee_layer=1, kappa=8,
+                                                               seed=52), n_layers=2)
+    w = case.w
+    need = msd.workspace_bytes(case.model.handle, w.batch, w.n_slots, w.kappa, case.capacity)
+    assert need > msd.MSD_STATIC_SCRATCH_BYTES
+    first = _verify(case, False)
+    _same(first, _verify(case, True), "static, M = 144")
+    assert np.isfinite(first["logits"]).all()
+    for kappa in (1, 4):
+        case.w = dataclasses.replace(w, kappa=kappa)
+        assert msd.workspace_bytes(case.model.handle, w.batch, w.n_slots, kappa, case.capacity) < need
+        other = _verify(case, False)
+        assert np.array_equal(first["logits"], other["logits"]) and np.array_equal(first["lse"], other["lse"])
+        assert np.array_equal(first["ids"][:, :kappa], other["ids"])
