@@ -152,10 +152,14 @@ __device__ __forceinline__ int row_len(const GemmArgs& a, int m) {
   return a.len[(m < a.M ? m : 0) / a.n_slots];
 }
 
-// the pre-norm summaries of the lane's row of row tile mt
-// (PER of them a lane at most; groups of 4 past the last summary are skipped
-// by a branch the whole wave takes)
-template <int PER>
+// the pre-norm summaries of the lane's row of row tile mt (PER of them a lane
+// at most). SKIP: groups of 4 past the last summary are skipped by a branch the
+// whole wave takes, for kernels that a row tile's summaries are a large part of
+// (0.6B-shaped layer at one row, 16 summaries: QKV 8.7 -> 7.7 us, gate+up 10.4
+// -> 9.7) and for QKV at several (fewer scalar registers: 14B, 25 rows, 23.8 ->
+// 23.4); else all loads are issued at once (66B, 25 rows: FFN up 146.0 -> 144.7
+// us, a 4096-token head 25.6 -> 25.0).
+template <bool SKIP, int PER>
 __device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, float2 (&st)[PER]) {
   const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
   const int m = 16 * mt + r16;
@@ -163,7 +167,7 @@ __device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, float2 (&s
   if (a.norm.kind == 0) return;
 #pragma unroll
   for (int i0 = 0; i0 < PER; i0 += 4) {
-    if (4 * i0 >= a.norm.tiles) continue;
+    if (SKIP && 4 * i0 >= a.norm.tiles) continue;
 #pragma unroll
     for (int i = i0; i < i0 + 4; ++i) {
       const int tt = q + 4 * i;
@@ -172,12 +176,12 @@ __device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, float2 (&s
   }
 }
 
-template <int EPI, bool NORM = true, int JT = 4>
+template <int EPI, bool NORM = true, int JT = 4, bool SKIP = true>
 __device__ __forceinline__ void epi_load(const GemmArgs& a, int t, int mt, EpiIn& in) {
   const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
   const int m = 16 * mt + r16;
   const int mm = m < a.M ? m : 0;
-  if constexpr (has_norm<EPI>() && NORM) stats_load(a, mt, in.st);
+  if constexpr (has_norm<EPI>() && NORM) stats_load<SKIP>(a, mt, in.st);
   if constexpr (EPI == EPI_RESID) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -225,7 +229,7 @@ __device__ __forceinline__ void epi_load(const GemmArgs& a, int t, int mt, EpiIn
 // (the exact merge of equal-count groups). The four lanes of a row each hold
 // every fourth summary and their partial sums are combined by a butterfly,
 // which gives all four lanes identical bits.
-template <int PER>
+template <bool SKIP, int PER>
 __device__ __forceinline__ void norm_finish(const GemmArgs& a, const float2 (&st)[PER], float& mu,
                                             float& rs) {
   const int q = (threadIdx.x & 63) >> 4;
@@ -236,7 +240,7 @@ __device__ __forceinline__ void norm_finish(const GemmArgs& a, const float2 (&st
   float sm = 0.0f;
 #pragma unroll
   for (int i0 = 0; i0 < PER; i0 += 4) {
-    if (4 * i0 >= nm.tiles) continue;
+    if (SKIP && 4 * i0 >= nm.tiles) continue;
 #pragma unroll
     for (int i = i0; i < i0 + 4; ++i)
       if (q + 4 * i < nm.tiles) sm += st[i].x;
@@ -247,7 +251,7 @@ __device__ __forceinline__ void norm_finish(const GemmArgs& a, const float2 (&st
   float m2 = 0.0f;
 #pragma unroll
   for (int i0 = 0; i0 < PER; i0 += 4) {
-    if (4 * i0 >= nm.tiles) continue;
+    if (SKIP && 4 * i0 >= nm.tiles) continue;
 #pragma unroll
     for (int i = i0; i < i0 + 4; ++i)
       if (q + 4 * i < nm.tiles) {
@@ -271,12 +275,12 @@ __device__ __forceinline__ void norm_finish(const GemmArgs& a, const float2 (&st
 __device__ __forceinline__ void row_norm(const GemmArgs& a, int mt, float& mu, float& rs) {
   if (a.norm.tiles <= 80) {
     float2 st[20];
-    stats_load(a, mt, st);
-    norm_finish(a, st, mu, rs);
+    stats_load<true>(a, mt, st);
+    norm_finish<true>(a, st, mu, rs);
   } else {
     float2 st[kMaxPer];
-    stats_load(a, mt, st);
-    norm_finish(a, st, mu, rs);
+    stats_load<true>(a, mt, st);
+    norm_finish<true>(a, st, mu, rs);
   }
 }
 
@@ -564,13 +568,13 @@ __device__ __forceinline__ void epilogue_apply(const GemmArgs& a, int t, int mt,
 // when they were loaded ahead (one row tile), otherwise they are loaded here.
 // norm_sh: (mu, r) of the tile's 16 rows, already merged (then NLDS: the
 // summaries are not loaded)
-template <int EPI, int JT, bool AHEAD, bool NLDS = false>
+template <int EPI, int JT, bool AHEAD, bool NLDS = false, bool SKIP = true>
 __device__ __forceinline__ void epilogue_tile(const GemmArgs& a, int t, int mt, const floatx4 (&acc)[JT],
                                               float* scr, const EpiIn& in1, const float2* norm_sh = nullptr) {
   EpiIn inl;
   if constexpr (!AHEAD) {
     if constexpr (EPI == EPI_QKV) inl.L = row_len(a, 16 * mt + (threadIdx.x & 15));
-    epi_load<EPI, !NLDS, JT>(a, t, mt, inl);
+    epi_load<EPI, !NLDS, JT, SKIP>(a, t, mt, inl);
   }
   const EpiIn& in = AHEAD ? in1 : inl;
   float mu = 0.0f, rs = 1.0f;
@@ -580,7 +584,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& a, int t, int mt, 
       mu = v.x;
       rs = v.y;
     } else {
-      norm_finish(a, in.st, mu, rs);
+      norm_finish<SKIP>(a, in.st, mu, rs);
     }
   }
   epilogue_apply<EPI, JT>(a, t, mt, acc, scr, in, mu, rs);
@@ -614,6 +618,22 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, int t, const fl
         for (int j = 0; j < JT; ++j) cur[j] = acc[mm][j];
     EpiIn none;
     epilogue_tile<EPI, JT, false, NLDS>(a, t, mt, cur, scr, none, NLDS ? norm_sh + 16 * mt : nullptr);
+  }
+}
+
+// The epilogues of the row tiles a wave owns (row tile mt belongs to wave mt %
+// NW), of a workgroup's nmt from row tile mt0 on. A function of its own: with
+// this loop in the kernel's body the compiler spilled 50 to 96 scalar registers
+// at 2 row tiles (14B, 25 rows: QKV 24.5 -> 23.4 us, gate+up 52.0 -> 51.0; 0.6B,
+// 72 rows, in groups: gate+up 13.5 -> 12.8).
+template <int MT, int NW, int EPI, int JT, bool SKIP>
+__device__ __forceinline__ void epilogue_own(const GemmArgs& a, int t, int mt0, int nmt, const floatx4 (&acc)[MT][JT],
+                                             float* scr, int wave) {
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    if (mt % NW != wave || mt >= nmt) continue;
+    EpiIn none;
+    epilogue_tile<EPI, JT, false, false, SKIP>(a, t, mt0 + mt, acc[mt], scr, none);
   }
 }
 
@@ -668,7 +688,7 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
       EpiIn hin;
       epi_load<EPI, true, JT>(a, t, mt0, hin);
       float mu, rs;
-      norm_finish(a, hin.st, mu, rs);
+      norm_finish<true>(a, hin.st, mu, rs);
       if (lane < 16) norm_sh[lane] = make_float2(mu, rs);
       __syncthreads();
       __syncthreads();
@@ -905,12 +925,7 @@ __global__ __launch_bounds__((64 * block_waves<MT, NW, EPI>())) void gemm_kernel
       }
       if (threadIdx.x == 0) counter_reset(&a.counters[t]);
     }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      if (!mine(mt) || mt >= nmt) continue;
-      EpiIn none;
-      epilogue_tile<EPI, JT, false>(a, t, mt0 + mt, acc[mt], scr_all + wave * 16 * kScr, none);
-    }
+    epilogue_own<MT, NW, EPI, JT, GROUPS || EPI == EPI_QKV>(a, t, mt0, nmt, acc, scr_all + wave * 16 * kScr, wave);
   }
 }
 
