@@ -206,7 +206,9 @@ typedef struct {
 } msd_ee_request;
 
 /* Workspace needed by msd_verify_block / msd_early_exit_topk / msd_accept
- * for this batch, block size, kappa and cache capacity. */
+ * for this batch, block size, kappa and cache capacity. It never falls when
+ * one of them grows: a workspace for a program's largest serves all smaller
+ * ones, and msd_early_exit_topk over up to batch * n_slots rows. */
 size_t msd_workspace_bytes(const msd_model* model, int32_t batch, int32_t n_slots,
                            int32_t kappa, int32_t capacity);
 

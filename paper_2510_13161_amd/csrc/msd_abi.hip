@@ -405,6 +405,7 @@ msd_status msd_model_create(const msd_model_config* cfg, const void* const* tens
     const int v = atoi(e);
     if (v >= 1 && v <= kMaxAttnChunks) m->attn_spans = v;
   }
+  plan_rows(m);
 
   // LayerNorm models: column sums c = W g and e = W b of every matrix that
   // consumes a LayerNorm output (q/k/v, the FFN up projections, the LM head),

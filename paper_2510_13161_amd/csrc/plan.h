@@ -20,8 +20,30 @@ namespace msd {
 constexpr size_t kStaticSplitBytes = (size_t)73 << 20;
 constexpr size_t kStaticScratchBytes = MSD_STATIC_SCRATCH_BYTES + kStaticSplitBytes;
 
-// What the plan depends on besides the block: the model, its device and the
-// launch-shape overrides.
+struct GemmShape {
+  int n_tiles, K, splits, waves, jt;
+  int wg_tiles = 1;
+  int row_groups = 0;
+  int split_from = 0;
+};
+
+struct Shapes {
+  GemmShape qkv, o, up, down, head;
+};
+
+// The GEMMs of a block of mt row tiles, and what the workspace keeps for them:
+// the most that any block of 1 .. mt row tiles uses, as split counts and tile
+// widths go up and down with the row tiles and a workspace sized for a program's
+// largest block has to serve its smaller ones.
+struct RowPlan {
+  Shapes s;
+  size_t part_bytes;       // split partials
+  int32_t split_tiles;     // split-K counters
+  int32_t head_tiles;      // column tiles of the head
+};
+
+// What a plan depends on besides the block: the model, its device and the
+// launch-shape overrides; and the plans of all row tile counts (plan_rows).
 struct PlanInputs {
   msd_model_config cfg;
   int32_t n_cus = 256;             // compute units of the model's device
@@ -35,15 +57,16 @@ struct PlanInputs {
   int32_t rows_narrow = 1;         // narrow GEMMs: many splits, deferred epilogue, or row groups
                                    // (0 off, 1 by weights, 2 many splits at any size)
   int32_t rows_narrow_mt = 3;      // row tiles from which it does
+  RowPlan rows[kMaxMT];            // of mt = 1 .. kMaxMT row tiles, at mt - 1
 };
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// 16-row tiles of M rows (1 .. kMaxMT). From 4 on every product of a padding
-// tile would be matrix-core time and power that the rows in use lack: at 7
-// tiles instead of 9 (99 rows) the 14B gate+up takes 100 -> 82 us, at 4
-// instead of 5 (63 rows) 72 -> 63.
-inline int row_tiles(int M) { return (M + 15) / 16; }
+// 16-row tiles of M rows, 1 .. kMaxMT (a block of more rows goes through no
+// GEMM). From 4 on every product of a padding tile would be matrix-core time and
+// power that the rows in use lack: at 7 tiles instead of 9 (99 rows) the 14B
+// gate+up takes 100 -> 82 us, at 4 instead of 5 (63 rows) 72 -> 63.
+inline int row_tiles(int64_t M) { return (int)std::min<int64_t>((M + 15) / 16, kMaxMT); }
 
 // Split-K factor. A workgroup streams its 1/s of a tile at about one
 // compute unit's rate, so a GEMM lasts as long as its busiest unit: W =
@@ -149,17 +172,6 @@ inline int rows_narrow_splits(const PlanInputs* m, int n_tiles, int K, int per_c
   }
   return best;
 }
-
-struct GemmShape {
-  int n_tiles, K, splits, waves, jt;
-  int wg_tiles = 1;
-  int row_groups = 0;
-  int split_from = 0;
-};
-
-struct Shapes {
-  GemmShape qkv, o, up, down, head;
-};
 
 // Wide GEMMs of more workgroups than one dispatch round takes (the LM head):
 // the rounds that are full run whole K, the workgroups of the last one are
@@ -284,6 +296,22 @@ inline Shapes shapes(const PlanInputs* m, int mt) {
   return s;
 }
 
+// Fills m->rows from the rest of *m: once per model.
+inline void plan_rows(PlanInputs* m) {
+  RowPlan most{};
+  for (int mt = 1; mt <= kMaxMT; ++mt) {
+    most.s = shapes(m, mt);
+    for (const GemmShape* g : {&most.s.qkv, &most.s.o, &most.s.up, &most.s.down, &most.s.head}) {
+      if (g->splits <= 1) continue;
+      const size_t part = (size_t)(g->n_tiles - g->split_from) * g->splits * mt * g->jt * 256 * sizeof(float);
+      most.part_bytes = std::max(most.part_bytes, part);
+      most.split_tiles = std::max(most.split_tiles, g->n_tiles);
+    }
+    most.head_tiles = std::max(most.head_tiles, most.s.head.n_tiles);
+    m->rows[mt - 1] = most;
+  }
+}
+
 struct Layout {
   Shapes s;
   size_t x, stats, q, img_x, img_h, img_f, img_attn, img_act, partial, counters, part_o, part_ml,
@@ -296,15 +324,16 @@ struct Layout {
 // image bytes of an [M][K] activation
 inline size_t img_bytes(int K, int MT) { return (size_t)(K / 32) * MT * 1024 * sizeof(uint16_t); }
 
+// The workspace of a block. No term falls with batch, n_slots, kappa or capacity.
 inline Layout layout(const PlanInputs* m, int batch, int n_slots, int kappa, int capacity) {
   const msd_model_config& c = m->cfg;
-  const int M = batch * n_slots;
-  const Shapes s = shapes(m, row_tiles(M));
+  const int64_t M = (int64_t)batch * n_slots;
   const int kmax = kappa > 1 ? kappa : 1;
   const int qd = c.n_heads * c.head_dim;
   Layout L{};
-  L.s = s;
   L.MT = row_tiles(M);
+  const RowPlan& rows = m->rows[L.MT - 1];
+  L.s = rows.s;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -315,27 +344,17 @@ inline Layout layout(const PlanInputs* m, int batch, int n_slots, int kappa, int
   L.stats = take((size_t)(c.d_model / kTileN) * M * sizeof(float2));
   // q as the attention's operand image: per sequence and kv head, the GQA
   // group's queries in 16-row tiles, hi + lo bf16 parts
-  const int q_tiles = ((c.n_heads / c.n_kv_heads) * n_slots + 15) / 16;
+  const int64_t q_tiles = ((int64_t)(c.n_heads / c.n_kv_heads) * n_slots + 15) / 16;
   L.q = take((size_t)batch * c.n_kv_heads * q_tiles * (c.head_dim / 32) * 1024 * sizeof(uint16_t));
   L.img_x = take(img_bytes(c.d_model, L.MT));
   L.img_h = take(img_bytes(c.d_model, L.MT));
   L.img_f = take(img_bytes(c.d_model, L.MT));
   L.img_attn = take(img_bytes(qd, L.MT));
   L.img_act = take(img_bytes(c.d_ffn, L.MT));
-  size_t part = 0;
-  int max_tiles = 0;
-  for (const GemmShape* g : {&s.qkv, &s.o, &s.up, &s.down, &s.head}) {
-    if (g->splits > 1) {
-      const size_t p = (size_t)(g->n_tiles - g->split_from) * g->splits * L.MT * g->jt * 256 * sizeof(float);
-      part = p > part ? p : part;
-      max_tiles = g->n_tiles > max_tiles ? g->n_tiles : max_tiles;
-    }
-  }
   // the GEMMs' split-K counters, then the attention's chunk counters (one per
   // sequence, kv head and query tile); all cleared by the rows kernel
-  const int attn_qt = ((c.n_heads / c.n_kv_heads) * n_slots + 15) / 16;
-  L.n_gemm_counters = max_tiles;
-  L.n_counters = max_tiles + (int64_t)batch * c.n_kv_heads * attn_qt;
+  L.n_gemm_counters = rows.split_tiles;
+  L.n_counters = rows.split_tiles + (int64_t)batch * c.n_kv_heads * q_tiles;
   L.counters = take((size_t)L.n_counters * sizeof(int32_t));
   L.max_chunks = (capacity + kAttnChunk - 1) / kAttnChunk;
   const size_t qn = (size_t)(c.n_heads / c.n_kv_heads) * n_slots;
@@ -348,13 +367,13 @@ inline Layout layout(const PlanInputs* m, int batch, int n_slots, int kappa, int
   L.part_ml = take(nparts * sizeof(float2));
   const size_t attn_end = off;
   off = shared;
-  L.partial = take(part);
+  L.partial = take(rows.part_bytes);
   off = std::max(off, attn_end);
   L.split_bytes = off - attn_end + align_up((size_t)L.n_counters * sizeof(int32_t)) -
                   align_up((size_t)(L.n_counters - L.n_gemm_counters) * sizeof(int32_t));
-  L.tile_ms = take((size_t)s.head.n_tiles * M * sizeof(float2));
-  L.tile_top = take((size_t)s.head.n_tiles * M * kmax * sizeof(uint64_t));
-  const int parts = head_parts(s.head.n_tiles);
+  L.tile_ms = take((size_t)rows.head_tiles * M * sizeof(float2));
+  L.tile_top = take((size_t)rows.head_tiles * M * kmax * sizeof(uint64_t));
+  const int parts = head_parts(rows.head_tiles);
   L.head_ms = take((size_t)parts * M * sizeof(float2));
   L.head_top = take((size_t)parts * M * kmax * sizeof(uint64_t));
   L.total = off;

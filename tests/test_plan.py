@@ -17,6 +17,7 @@ using namespace msd;
 extern "C" void plan_blocks(const msd_model_config* cfg, const int32_t* blocks, int64_t n, int64_t* out) {
   PlanInputs in;
   in.cfg = *cfg;
+  plan_rows(&in);
   for (int64_t i = 0; i < n; ++i) {
     const int32_t* b = blocks + 4 * i;
     const Layout L = layout(&in, b[0], b[1], b[2], b[3]);
@@ -84,6 +85,18 @@ def test_early_exit_entry_point_runs_in_the_verify_workspace(plan, model):
             for c in CAPACITIES:
                 verify = plan(model, [(b, n, k, c) for b in batches])[:, 0]
                 assert (own <= verify).all(), (model, n, k, c, np.argmax(own > verify) + 1)
+
+
+@pytest.mark.parametrize("model", sorted(MODELS))
+def test_workspace_never_falls_with_a_larger_block(plan, model):
+    """A workspace for the largest block serves every smaller one: the size
+    does not fall with batch, slots, early-exit width or capacity (up to
+    blocks of more rows than a verify pass takes, which acceptance takes)."""
+    batches, slots = range(1, MAX_ROWS + 9), (1, 2, 3, 5, 8, 9, 16, 17, 25, 33, 48, 49, 63, 64)
+    grid = [(b, n, k, c) for b in batches for n in slots for k in KAPPAS for c in CAPACITIES]
+    t = plan(model, grid)[:, 0].reshape(len(batches), len(slots), len(KAPPAS), len(CAPACITIES))
+    for axis in range(4):
+        assert (np.diff(t, axis=axis) >= 0).all(), (model, ("batch", "slots", "kappa", "capacity")[axis])
 
 
 @pytest.mark.parametrize("model", sorted(MODELS))

@@ -127,3 +127,49 @@ def test_static_scratch_with_split_partials_past_its_size():
         other = _verify(case, False)
         assert np.array_equal(first["logits"], other["logits"]) and np.array_equal(first["lse"], other["lse"])
         assert np.array_equal(first["ids"][:, :kappa], other["ids"])
+
+
+def test_one_workspace_for_the_largest_block():
+    """A workspace sized for a program's largest block serves every smaller
+    one, with and without the early-exit message, and the early-exit entry
+    point over the same rows: each call succeeds there and has the bits of a
+    call with a workspace of its own size. 6 row counts, 1 to 4 row tiles; the
+    3-tile kernels of these widths use more split partials than the 4-tile
+    ones."""
+    torch = _torch()
+    from paper_2510_13161_amd import msd
+    shape = synth.ModelShape("gqa", 2, 1024, 16, 4, 64, 2048, 16000)
+    B, n, kappa, cap = 6, 9, 4, 256
+    case = H.GpuCase(synth.WORKLOADS["14b_batch16"].with_model(shape, batch=B, ctx=(40, 200), ee_layer=1, kappa=kappa,
+                                                               seed=53), capacity=cap)
+    h, V = case.model.handle, shape.vocab
+    tokens = torch.from_numpy(case.si.tokens).cuda()
+    shared = torch.empty(msd.workspace_bytes(h, B, n, kappa, cap), dtype=torch.uint8, device="cuda")
+    hidden = torch.randn((B * n, shape.d_model), generator=torch.Generator().manual_seed(54)).cuda()
+
+    def run(b, message, ws):
+        M = b * n
+        out = dict(logits=torch.full((M, V), -7.0, device="cuda"),
+                   argmax=torch.full((M,), -7, dtype=torch.int32, device="cuda"),
+                   lse=torch.full((M,), -7.0, device="cuda"),
+                   ids=torch.full((M, kappa), -7, dtype=torch.int32, device="cuda"),
+                   logp=torch.full((M, kappa), -7.0, device="cuda"))
+        case.reset_len()
+        ee = msd.EERequest(1, kappa, out["ids"].data_ptr(), out["logp"].data_ptr(), None) if message else None
+        msd.verify_block(h, case.cache.c, msd.make_block(tokens[:b].contiguous()), ee, out["logits"], out["argmax"],
+                         out["lse"], ws)
+        if not message:
+            msd.early_exit_topk(h, hidden[:M].contiguous(), kappa, out["ids"], out["logp"], ws)
+        torch.cuda.synchronize()
+        assert int(case.cache.status.item()) == 0
+        return {k: v.cpu().numpy() for k, v in out.items()}
+
+    for b in range(B, 0, -1):
+        for message in (True, False):
+            own = torch.empty(msd.workspace_bytes(h, b, n, kappa if message else 1, cap) if message else
+                              max(msd.workspace_bytes(h, b, n, 1, cap), msd.workspace_bytes(h, 1, b * n, kappa, 1)),
+                              dtype=torch.uint8, device="cuda")
+            want, got = run(b, message, own), run(b, message, shared)
+            for k in want:
+                assert np.array_equal(want[k], got[k]), (b, message, k)
+            assert np.isfinite(got["logits"]).all() and (got["ids"] >= 0).all()
