@@ -1137,7 +1137,7 @@ __global__ __launch_bounds__(64 * (NW + 1), rows_waves_per_simd<MT>()) void gemm
 
   if (splits > 1) {
     // this split's partial of the tile (all row tiles); gemm_epi_kernel sums
-    // the splits in split order and runs the epilogue
+    // the splits in a fixed order and runs the epilogue
     float* part = a.partial + ((size_t)(t - a.split_from) * splits + s) * TF + lane * 4;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)

@@ -103,7 +103,7 @@ inline int splits_for(const PlanInputs* m, int n_tiles, int K, int waves, int pe
 
 // Several row tiles, wide GEMMs (256 or more 64-column tiles): 4 tiles a
 // workgroup sharing the activation through LDS (one workgroup per compute
-// unit from 5 row tiles on, by its LDS ring and registers; two up to 3).
+// unit from 4 row tiles on, by its LDS ring and registers; two up to 3).
 // Splits of K as for split-K above, for the best balance of
 // ceil(n_tiles / 4) * s workgroups over the units within two workgroups a unit
 // (one dispatch round, or two from 4 row tiles on: 66B FFN up, 144 workgroup

@@ -368,18 +368,25 @@ def test_tiny_wide_early_exit_message(kappa):
 
 @pytest.mark.parametrize("which,M,kappa", [("tiny", 9, 8), ("tiny", 144, 4), ("14b", 9, 8),
                                              ("14b", 144, 4), ("14b", 9, 32), ("14b", 144, 13),
-                                             ("14b", 9, 1)])
+                                             ("14b", 9, 1), ("14b", 33, 4), ("14b", 100, 4),
+                                             ("ragged", 33, 4), ("ragged", 48, 8), ("ragged", 49, 4),
+                                             ("ragged", 80, 4), ("ragged", 81, 4), ("ragged", 112, 4),
+                                             ("ragged", 113, 4), ("ragged", 144, 4), ("ragged", 144, 32)])
 def test_early_exit_topk_entry_point(which, M, kappa):
     """msd_early_exit_topk on its own (the Sec. 3.1 token channel from a
     residual): seeded fp32 residual rows, final norm, LM head and top-kappa
     with log-probabilities, at one row tile (M = 9) and at the batch-16 block
     size (M = 144, nine row tiles), checked row by row against the oracle's
     head on the same rows (check_ee_message); every merge width (kappa 1, up
-    to 8, up to 32) over the 14B vocabulary's 5 or 10 merge parts."""
+    to 8, up to 32) over the 14B vocabulary's 5 or 10 merge parts. From 3 row
+    tiles on the workgroups of the last dispatch round are split in K: at 3 (two
+    workgroups a compute unit) and 4 to 9 row tiles, and, with a LayerNorm, over
+    a vocabulary whose last column tile is masked and alone in its workgroup."""
     torch = _torch()
     import oracle as orc
     from paper_2510_13161_amd import msd
-    shape = synth.TINY if which == "tiny" else synth.QWEN14B.with_layers(1)
+    shape = {"tiny": synth.TINY, "14b": synth.QWEN14B.with_layers(1),
+             "ragged": synth.ModelShape("ragged", 1, 1024, 8, 2, 128, 1024, 148240, norm="layer")}[which]
     seed = 31
     model = msd.Model(shape, synth.device_weights(shape, seed), max_positions=64)
     g = np.random.default_rng(32 + M)

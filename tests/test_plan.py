@@ -31,6 +31,8 @@ extern "C" void plan_blocks(const msd_model_config* cfg, const int32_t* blocks, 
 """
 
 MODELS = {"tiny": synth.TINY, "0.6b": synth.DRAFT06B, "14b": synth.QWEN14B, "66b": synth.OPT66B,
+          # the head whose last dispatch round is split, over a ragged vocabulary
+          "ragged": synth.ModelShape("ragged", 1, 1024, 8, 2, 128, 1024, 148240, norm="layer"),
           # a small head at one row tile; a wide ungated FFN
           "gqa": synth.ModelShape("gqa", 4, 1024, 16, 4, 64, 2048, 16000),
           "wide": synth.ModelShape("wide", 4, 10240, 80, 8, 128, 40960, 250000, norm="layer", act="relu")}
@@ -116,3 +118,14 @@ def test_static_scratch_holds_what_its_documented_size_holds(plan, model):
     ("0.6b", (16, 9, 32, 64), 0), ("66b", (16, 9, 1, 2048), 0)])
 def test_static_scratch_at_its_bound(plan, model, block, fits):
     assert plan(model, [block])[0, 1] == fits
+
+
+@pytest.mark.parametrize("model,rows,splits", [("14b", 33, 6), ("14b", 49, 3), ("14b", 144, 3), ("ragged", 33, 4),
+                                               ("ragged", 48, 4), ("ragged", 49, 3), ("ragged", 144, 3)])
+def test_last_dispatch_round_of_the_head_is_split(plan, model, rows, splits):
+    """The head of 33 rows and more over a large vocabulary: whole K in the full
+    dispatch rounds, splits of K in the last one, for every early-exit width."""
+    for kappa in KAPPAS:
+        n_tiles, _, s, _, _, wg_tiles, _, split_from = plan(model, [(1, rows, kappa, 64)])[0, 2 + 4 * 8:]
+        assert (s, wg_tiles) == (splits, 4) and 0 < split_from < n_tiles and split_from % 4 == 0
+    assert model != "ragged" or n_tiles % 4 == 1
