@@ -154,11 +154,9 @@ __device__ __forceinline__ int row_len(const GemmArgs& a, int m) {
 
 // the pre-norm summaries of the lane's row of row tile mt (PER of them a lane
 // at most). SKIP: groups of 4 past the last summary are skipped by a branch the
-// whole wave takes, for kernels that a row tile's summaries are a large part of
-// (0.6B-shaped layer at one row, 16 summaries: QKV 8.7 -> 7.7 us, gate+up 10.4
-// -> 9.7) and for QKV at several (fewer scalar registers: 14B, 25 rows, 23.8 ->
-// 23.4); else all loads are issued at once (66B, 25 rows: FFN up 146.0 -> 144.7
-// us, a 4096-token head 25.6 -> 25.0).
+// whole wave takes (0.6B-shaped layer at one row, 16 summaries: QKV 8.7 -> 7.7
+// us, gate+up 10.4 -> 9.7; QKV at several row tiles, 14B, 25 rows, 23.8 -> 23.4);
+// else all loads are issued at once.
 template <bool SKIP, int PER>
 __device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, float2 (&st)[PER]) {
   const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
@@ -176,12 +174,12 @@ __device__ __forceinline__ void stats_load(const GemmArgs& a, int mt, float2 (&s
   }
 }
 
-template <int EPI, bool NORM = true, int JT = 4, bool SKIP = true>
+template <int EPI, bool NORM = true, int JT = 4>
 __device__ __forceinline__ void epi_load(const GemmArgs& a, int t, int mt, EpiIn& in) {
   const int lane = threadIdx.x & 63, q = lane >> 4, r16 = lane & 15;
   const int m = 16 * mt + r16;
   const int mm = m < a.M ? m : 0;
-  if constexpr (has_norm<EPI>() && NORM) stats_load<SKIP>(a, mt, in.st);
+  if constexpr (has_norm<EPI>() && NORM) stats_load<true>(a, mt, in.st);
   if constexpr (EPI == EPI_RESID) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -281,6 +279,25 @@ __device__ __forceinline__ void row_norm(const GemmArgs& a, int mt, float& mu, f
     float2 st[kMaxPer];
     stats_load<true>(a, mt, st);
     norm_finish<true>(a, st, mu, rs);
+  }
+}
+
+// The same in the epilogues of several row tiles without groups, where the
+// branches of the groups cost more than they skip (66B, 25 rows: FFN up 146.0 ->
+// 144.7 us). The head alone has one branch for rows of up to 1024 columns, as a
+// wide vocabulary over so short a K is bound by its epilogues (0.6B, 25 rows: 73
+// -> 64.5 us; 14B 280.5 either way); elsewhere it costs more than it saves (14B
+// gate+up 50.7 -> 51.3).
+template <int EPI>
+__device__ __forceinline__ void row_norm_at_once(const GemmArgs& a, int mt, float& mu, float& rs) {
+  if (EPI == EPI_HEAD && a.norm.tiles <= 16) {
+    float2 st[4];
+    stats_load<false>(a, mt, st);
+    norm_finish<false>(a, st, mu, rs);
+  } else {
+    float2 st[kMaxPer];
+    stats_load<false>(a, mt, st);
+    norm_finish<false>(a, st, mu, rs);
   }
 }
 
@@ -574,7 +591,7 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& a, int t, int mt, 
   EpiIn inl;
   if constexpr (!AHEAD) {
     if constexpr (EPI == EPI_QKV) inl.L = row_len(a, 16 * mt + (threadIdx.x & 15));
-    epi_load<EPI, !NLDS, JT, SKIP>(a, t, mt, inl);
+    epi_load<EPI, !NLDS && SKIP, JT>(a, t, mt, inl);
   }
   const EpiIn& in = AHEAD ? in1 : inl;
   float mu = 0.0f, rs = 1.0f;
@@ -583,8 +600,10 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& a, int t, int mt, 
       const float2 v = norm_sh[threadIdx.x & 15];
       mu = v.x;
       rs = v.y;
+    } else if constexpr (SKIP) {
+      norm_finish<true>(a, in.st, mu, rs);
     } else {
-      norm_finish<SKIP>(a, in.st, mu, rs);
+      row_norm_at_once<EPI>(a, mt, mu, rs);
     }
   }
   epilogue_apply<EPI, JT>(a, t, mt, acc, scr, in, mu, rs);
