@@ -132,10 +132,18 @@ struct AttnShape {
 // kAttnPlanSpans spans or more: a workgroup per compute unit (the ring fills
 // its LDS) and chunks that the device sizes from the lengths, as chunks sized
 // for the capacity leave the units of short sequences idle while a long one's
-// run on (14B batch 16 at 512 to 8192: 85.9 -> 73.3 us; the tree's one
-// sequence at 4096: 14.3 -> 12.7). Below, counting costs what it gains (8 at
-// 1024, 2 spans: 16.1 against 17.0 us; 11 at 256 to 4096, 6 spans: 38.5
-// against 35.9). m->attn_spans > 0: chunks of that many spans.
+// run on (14B batch 16, three draws of lengths from 512 to 8192: 102.9, 111.9 and
+// 81.4 us with chunks for the capacity, 89.8, 110.5 and 73.6 planned; the tree's
+// one sequence at 4096: 14.3 and 12.7). The line, from chains of 9 at 14B
+// widths, 2 to 15 sequences of up to 700 to 7500 positions, time with chunks for
+// the capacity over time planned, merge included:
+//   spans   all of one length   lengths from 1/8 up   one long, the others 1/8
+//   2       0.89-1.00           0.84-1.10             0.87-1.17
+//   3-5     0.92-1.41           0.92-1.58             0.96-1.48
+//   6-7     0.95-1.47           1.02-1.61             1.03-1.49
+//   9-15    0.95-1.45           1.03-1.58             1.37-1.93
+// so from 6 on only equal lengths can lose, 5 % at most.
+// m->attn_spans > 0: chunks of that many spans.
 constexpr int kAttnPlanSpans = 6;
 AttnShape attn_shape(const msd_model* m, int max_chunks, int n_kv_heads, int batch, int q_tiles,
                      int head_dim) {
@@ -157,7 +165,10 @@ AttnShape attn_shape(const msd_model* m, int max_chunks, int n_kv_heads, int bat
 // the ring kernel's workgroups (m->attn_defer: -1 that rule, 0 never, 1
 // always). Measured: the 14B tree (9 chunks of 2 spans) 8.62 -> 8.30 ms per
 // step; where the last-arrival merge is short (the chain's 5 one-span chunks, 2
-// or 3 chunks at batch 16 and the 66B tree) the extra launch does not pay.
+// or 3 chunks at batch 16 and the 66B tree) the extra launch does not pay. A long
+// sequence among short ones may own more of the planned chunks than the average
+// that this rule sees; its last arrival then merges them (included in the last
+// column above).
 constexpr int kAttnDeferChunks = 6;
 bool attn_defer(const msd_model* m, int max_chunks, int batch, const AttnShape& s) {
   const int chunks = s.ring ? std::min(s.wgs / batch, max_chunks) : (max_chunks + s.nb - 1) / s.nb;
